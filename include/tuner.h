@@ -51,7 +51,11 @@ enum { TUNER_SCALE_LINEAR = 0, TUNER_SCALE_LOG2 = 1 };
 enum { TUNER_FP32 = 0, TUNER_BF16_MFMA = 1 };
 /*
  * How a TUNER_FP32 network is evaluated (all meet the fp32 tolerance of 1e-5):
- *   AUTO     the library's choice (currently MFMA)
+ *   AUTO     the library's choice, by the sizes of the space and the networks: first layers as a
+ *            product of two tabulated exponentials in fp32, second hidden layers on the f16 matrix
+ *            instructions with every operand split into two planes (tiles of weights that two
+ *            planes do not hold well keep the fp32 instructions), or MFMA; its error against
+ *            exact arithmetic is that of MFMA or less
  *   MFMA     fp32 matrix instructions, fp32 accumulate
  *   VALU     plain vector-ALU FMAs, one configuration per lane, weights broadcast from LDS
  *   SPLIT16  every operand split into two f16 planes (22 significand bits), three f16
@@ -151,7 +155,8 @@ size_t tuner_workspace_bytes(const tuner_space* space, const tuner_model* model,
  * their share of the layer-1 pre-activations once per tile instead of once per
  * configuration.  *n_hoisted receives the number of such parameters this library
  * treats that way (0: none; always 0 for the other network evaluations and for
- * tuner_predict_indices).
+ * tuner_predict_indices).  TUNER_ALGO_AUTO, which may split layer 1 elsewhere, reports the figure
+ * of TUNER_ALGO_MFMA here, in tuner_tabulated_parameters and in tuner_sweep_plan's layer1.
  */
 int tuner_hoisted_parameters(const tuner_space* space, const tuner_model* model, int32_t* n_hoisted);
 
@@ -179,7 +184,7 @@ int tuner_tabulated_parameters(const tuner_space* space, const tuner_model* mode
  * tuner_predict_topk.  Errors as for those calls, minus the workspace.
  */
 typedef struct {
-  int32_t network;                /* 0 fp32 matrix, 1 bf16 matrix, 2 two-plane f16 matrix, 3 vector ALU */
+  int32_t network;                /* 0 fp32 (AUTO, MFMA), 1 bf16 matrix, 2 two-plane f16 matrix, 3 vector ALU */
   int32_t layer1;                 /* 0 plain; 1 tile-constant parameters once per tile; 2 also the rest from a table */
   int32_t waves;                  /* waves per workgroup */
   int32_t tile;                   /* configurations per tile */

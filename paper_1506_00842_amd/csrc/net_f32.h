@@ -123,6 +123,7 @@ struct F32Net {
   // points that slot of the table at the constant)
   static constexpr bool kBiasInput = true;
   static constexpr bool kHoist = false;
+  static constexpr bool kRows = false;
   static __device__ __forceinline__ void load_features(const DevSpace& sp, uint32_t i, int lane, bool pow2,
                                                        const NetOffsets&, Feat& f) {
     const int h = lane >> 5;
@@ -142,8 +143,14 @@ struct F32Net {
   static __device__ __forceinline__ float forward(const uint32_t* __restrict__ wm, const Feat& f, int lane,
                                                   const NetOffsets& o) {
     const float* w = reinterpret_cast<const float*>(wm);
-    const int h = lane >> 5;
     floatx16 a1[NT1];
+    layer1(w, f, lane, o, nullptr, nullptr, a1);
+    return f32_after_layer1<NT1, NT2>(w, a1, lane, o);
+  }
+
+  // pre-activations of layer 1
+  static __device__ __forceinline__ void layer1(const float* __restrict__ w, const Feat& f, int lane, const NetOffsets& o,
+                                                const float*, float*, floatx16 (&a1)[NT1]) {
 #pragma unroll
     for (int t = 0; t < NT1; ++t)
 #pragma unroll
@@ -169,7 +176,6 @@ struct F32Net {
         a1[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, f.x[KS1 - 1], a1[t], 0, 0, 0);
       }
     }
-    return f32_after_layer1<NT1, NT2>(w, a1, lane, o);
   }
 };
 

@@ -27,6 +27,7 @@ template <int KSL, int NT1, int NT2>
 struct F32HNet {
   static constexpr int kTile = 32;
   static constexpr bool kHoist = true;
+  static constexpr bool kRows = false;
   static constexpr int kUnits = NT1 * 32;
   static constexpr int kScratchZ = kUnits < 64 ? 64 : kUnits;   // floats of the z_high scratch
   struct Feat { float x[KSL]; };   // B operand of layer 1: feature of parameter p0 + 2 s + h
@@ -63,6 +64,14 @@ struct F32HNet {
   static __device__ __forceinline__ float forward(const uint32_t* __restrict__ wm, const Feat& f, int lane,
                                                   const NetOffsets& o, const float* xs, float* zs) {
     const float* w = reinterpret_cast<const float*>(wm);
+    floatx16 a1[NT1];
+    layer1(w, f, lane, o, xs, zs, a1);
+    return f32_after_layer1<NT1, NT2>(w, a1, lane, o);
+  }
+
+  // pre-activations of layer 1
+  static __device__ __forceinline__ void layer1(const float* __restrict__ w, const Feat& f, int lane, const NetOffsets& o,
+                                                const float* xs, float* zs, floatx16 (&a1)[NT1]) {
     const int h = lane >> 5;
     // the low parameters' weights first, where the register budget allows (the 128-wide
     // variants run 2 waves per SIMD): their reads are in flight while z_high is summed
@@ -109,7 +118,6 @@ struct F32HNet {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    floatx16 a1[NT1];
 #pragma unroll
     for (int t = 0; t < NT1; ++t)
 #pragma unroll
@@ -130,7 +138,6 @@ struct F32HNet {
         if (4 * sg + 3 < KSL) a1[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, f.x[(4 * sg + 3) % KSL], a1[t], 0, 0, 0);
       }
     }
-    return f32_after_layer1<NT1, NT2>(w, a1, lane, o);
   }
 };
 

@@ -21,7 +21,7 @@ enum { MODE_TOPK = 0, MODE_ALL = 1 };
 // validity of the configurations of one chunk, known before the sweep
 enum { CHUNK_ALL_INVALID = 0, CHUNK_ALL_VALID = 1, CHUNK_MIXED = 2 };
 // how the network is evaluated
-enum { NET_F32_MFMA = 0, NET_BF16 = 1, NET_F16X2 = 2, NET_F32_VALU = 3 };
+enum { NET_F32_MFMA = 0, NET_BF16 = 1, NET_F16X2 = 2, NET_F32_VALU = 3, NET_F32_SPLIT = 4 };
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
@@ -49,9 +49,19 @@ struct Shape {
   int hoist;                  // 0: no; 1: high share once per tile (net_f32h.h); 2: also the low share from a table (net_f32t.h)
   int p0;                     // parameters 0 .. p0-1 are constant over a tile of 32 configurations
   int o_wh;                   // their weights and the bias (layout of the network's header)
+  // two-plane fp32 network (net_split.h)
+  int o_flags;
+  int span;                   // > 0: factored first layer; configurations per row
+  int rows;                   // ... and the most rows a wave's tiles reach
 };
 
-struct NetOffsets { int w1, w2, b1, b2, wo, h1, h2, wh, p0; };   // word offsets; real hidden widths; hoisting
+struct NetOffsets {
+  int w1, w2, b1, b2, wo, h1, h2, wh, p0;      // word offsets; real hidden widths; hoisting
+  int flags;                                   // two-plane networks
+  uint32_t span, span_magic;                   // factored first layer: span; ceil(2^16 / span) divides places < 256
+  uint32_t span_mul, span_sh;                  // division constants of the span (fast_div)
+  uint32_t rows;                               // rows of the per-wave scratch
+};
 
 struct SweepParams {
   uint64_t begin, count;
@@ -96,6 +106,7 @@ struct Variant { int net, KS, NT1, NT2, R, waves, tile; SweepFn fn; };
 const Variant* find_variant_f32(int KS, int NT1, int NT2);
 const Variant* find_variant_f32h(int KSL, int NT1, int NT2);
 const Variant* find_variant_f32t(int NT1, int NT2);
+const Variant* find_variant_split(const Shape& sh);
 const Variant* find_variant_lp(int net, int KS, int NT1, int NT2);
 const Variant* find_variant_valu(int KS, int NT1, int NT2);
 

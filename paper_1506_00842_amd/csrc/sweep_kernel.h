@@ -99,6 +99,10 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
   // per-wave scratch of the hoisting network: the tiles' high features, then one z_high vector
   float* hoist_xs = nullptr;
   float* hoist_zs = nullptr;
+  if constexpr (Net::kRows) {
+    hoist_xs = reinterpret_cast<float*>(smem + prm.hoist_offset) + (size_t)wave_u * prm.off.rows * (32 + Net::kRowFloats);
+    hoist_zs = hoist_xs + prm.off.rows * 32;
+  }
   if constexpr (Net::kHoist) {
     hoist_xs = reinterpret_cast<float*>(smem + prm.hoist_offset) + (size_t)wave_u * (R * 32 + Net::kScratchZ);
     hoist_zs = hoist_xs + R * 32;
@@ -224,6 +228,16 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
     float ysum[R];
     bool ok[R], any[R];
     uint32_t idx[R];
+    // factored networks: the rows (configurations that share all but their last parameters)
+    // that the wave's tiles reach
+    uint32_t row0 = 0, place0 = 0, n_rows = 0;
+    bool any_tile = false;
+    if constexpr (Net::kRows) {
+      const uint32_t i0 = (uint32_t)(prm.begin + (uint64_t)chunk * kIter) + (uint32_t)(wave_u * r_used * kTile);
+      row0 = fast_div(i0, prm.off.span_mul, prm.off.span_sh);
+      place0 = i0 - row0 * prm.off.span;
+      n_rows = (((place0 + (uint32_t)(r_used * kTile) - 1u) * prm.off.span_magic) >> 16) + 1u;
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       // uniform: tile start inside the range, and how many of its configurations exist
@@ -250,12 +264,19 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
       ok[r] = v;
       any[r] = __ballot(v) != 0ull;
       ysum[r] = 0.0f;
-      if (any[r]) {
+      if constexpr (Net::kRows) {
+        Net::place(place0 + (uint32_t)(r * kTile + c), lane, prm.off, feat[r]);
+        any_tile = any_tile || any[r];
+      } else if (any[r]) {
         Net::load_features(sp, i, lane, pow2, prm.off, feat[r]);
         if constexpr (Net::kHoist) Net::load_high(sp, i, lane, pow2, prm.off, hoist_xs + r * 32);
       } else {
         Net::zero_features(feat[r]);
       }
+    }
+
+    if constexpr (Net::kRows) {
+      if (any_tile) Net::load_rows(sp, row0, n_rows, lane, pow2, prm.off, hoist_xs);
     }
 
     // ---- ensemble
@@ -280,10 +301,14 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
       nm = nm < prm.members_per_stage ? nm : prm.members_per_stage;
       for (int m = 0; m < nm; ++m) {
         const uint32_t* w = stage + (size_t)m * prm.member_words;
+        if constexpr (Net::kRows) {
+          if (any_tile) Net::rows(w, n_rows, lane, prm.off, hoist_xs, hoist_zs);
+        }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           if (any[r]) {
-            if constexpr (Net::kHoist) ysum[r] += Net::forward(w, feat[r], lane, prm.off, hoist_xs + r * 32, hoist_zs);
+            if constexpr (Net::kRows) ysum[r] += Net::forward(w, feat[r], lane, prm.off, hoist_zs);
+            else if constexpr (Net::kHoist) ysum[r] += Net::forward(w, feat[r], lane, prm.off, hoist_xs + r * 32, hoist_zs);
             else ysum[r] += Net::forward(w, feat[r], lane, prm.off);
           }
         }

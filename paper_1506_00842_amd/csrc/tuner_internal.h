@@ -29,6 +29,9 @@ namespace tuner {
 int set_error(int code, const std::string& msg);
 int hip_error(hipError_t e, const char* what);
 
+// Multiply-shift constants for unsigned 32-bit division by d >= 1 (fast_div).
+void div_constants(uint32_t d, uint32_t* mul, uint32_t* sh);
+
 // Raises a kernel's dynamic-LDS limit to at least `bytes` on the current device.  The
 // driver call is made only when the limit has to grow: it is a host round trip of several
 // microseconds, which a short sweep would pay on every call.

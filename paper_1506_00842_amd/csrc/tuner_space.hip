@@ -51,7 +51,7 @@ static int ceil_log2(uint64_t d) {
 }
 
 // Multiply-shift constants for unsigned 32-bit division by d >= 1.
-static void div_constants(uint32_t d, uint32_t* mul, uint32_t* sh) {
+void div_constants(uint32_t d, uint32_t* mul, uint32_t* sh) {
   const int l = ceil_log2(d);
   const uint64_t two_l = 1ull << l;  // l <= 32
   const unsigned __int128 num = (unsigned __int128)(two_l - d) << 32;

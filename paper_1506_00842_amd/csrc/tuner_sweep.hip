@@ -28,6 +28,7 @@
 #include "net_f32h.h"
 #include "net_f32t.h"
 #include "net_lp.h"
+#include "net_split.h"
 #include "net_valu.h"
 #include "sweep_common.h"
 #include "tuner_internal.h"
@@ -48,6 +49,39 @@ struct PrepParams {
   WsHeader* hdr;
 };
 
+// bias_slot: the plain fp32 matrix layer 1 reads its bias column's constant 1 as the feature of
+// the slot after the last parameter (same thread as the plain copy of that word).
+__device__ __forceinline__ void write_tables_and_header(const DevSpace& sp, const PrepParams& pp, bool bias_slot,
+                                                        uint32_t gtid, uint32_t gsize) {
+  const Shape& sh = pp.sh;
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(&sp);
+  uint32_t* dst = reinterpret_cast<uint32_t*>(pp.space_out);
+  for (uint32_t x = gtid; x < sizeof(DevSpace) / 4; x += gsize) dst[x] = src[x];
+  if (bias_slot) {
+    const uint32_t word = (uint32_t)((const char*)&sp.pa[sh.P].lut_off4 - (const char*)&sp) / 4u;
+    if (gtid == word % gsize) pp.space_out->pa[sh.P].lut_off4 = 4u * (uint32_t)kLutOne;
+  }
+  // header: the idle state every sweep starts from and its last workgroup restores
+  if (gtid < 64) {
+    // the output biases, 64 loads at a time, added in member order
+    const int r_bo = sh.raw_member_floats - 1;
+    float bo = 0.0f;
+    for (int e0 = 0; e0 < sh.E; e0 += 64) {
+      const int e = e0 + (int)gtid;
+      const float v = e < sh.E ? pp.raw[(size_t)e * sh.raw_member_floats + r_bo] : 0.0f;
+      const int n = sh.E - e0 < 64 ? sh.E - e0 : 64;
+      for (int i = 0; i < n; ++i) bo += __shfl(v, i);
+    }
+    if (gtid != 0) return;
+    pp.hdr->bo_sum = bo;
+    pp.hdr->work_counter = 0u;
+    pp.hdr->n_live = 0u;
+    pp.hdr->done = 0u;
+    pp.hdr->merge_done = 0u;
+    pp.hdr->tau = kKeyMax;
+  }
+}
+
 __global__ void __launch_bounds__(256) prep_kernel(const DevSpace sp, const PrepParams pp) {
   const Shape& sh = pp.sh;
   const uint32_t gtid = blockIdx.x * blockDim.x + threadIdx.x;
@@ -66,30 +100,45 @@ __global__ void __launch_bounds__(256) prep_kernel(const DevSpace sp, const Prep
     else word = __float_as_uint(pack_word_f32(sh, raw, q));
     pp.packed[x] = word;
   }
-  // space tables
-  {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(&sp);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(pp.space_out);
-    for (uint32_t x = gtid; x < sizeof(DevSpace) / 4; x += gsize) dst[x] = src[x];
-    // the fp32 matrix network reads its bias column's constant 1 as the feature of the
-    // slot after the last parameter (same thread as the plain copy of that word)
-    if (sh.net == NET_F32_MFMA && !sh.hoist) {
-      const uint32_t word = (uint32_t)((const char*)&sp.pa[sh.P].lut_off4 - (const char*)&sp) / 4u;
-      if (gtid == word % gsize) pp.space_out->pa[sh.P].lut_off4 = 4u * (uint32_t)kLutOne;
+  write_tables_and_header(sp, pp, sh.net == NET_F32_MFMA && !sh.hoist, gtid, gsize);
+}
+
+// The same for the two-plane networks (net_split.h): the first workgroups write a slice of a
+// member's factored first layer each, the next a 32-row tile of a second layer each, the rest
+// the words that stand for themselves, the space tables and the header.
+__global__ void __launch_bounds__(256) prep_split_kernel(const DevSpace sp, const PrepParams pp) {
+  __shared__ PackScratch scratch;
+  const Shape& sh = pp.sh;
+  const uint32_t slices = (uint32_t)split_table_slices(sh);
+  const uint32_t n_tables = (uint32_t)sh.E * slices, n_tiles = (uint32_t)(sh.E * sh.NT2);
+  uint32_t b = blockIdx.x;
+  if (b < n_tables) {
+    const uint32_t e = b / slices;
+    pack_factored(sh, pp.raw + (size_t)e * sh.raw_member_floats, pp.packed + (size_t)e * sh.member_words, sp,
+                  (int)(b - e * slices), scratch);
+    return;
+  }
+  b -= n_tables;
+  if (b < n_tiles) {
+    const uint32_t e = b / sh.NT2;
+    pack_split_w2(sh, pp.raw + (size_t)e * sh.raw_member_floats, pp.packed + (size_t)e * sh.member_words,
+                  (int)(b - e * sh.NT2), scratch);
+    return;
+  }
+  b -= n_tiles;
+  const uint32_t gtid = b * 256u + threadIdx.x, gsize = (gridDim.x - n_tables - n_tiles) * 256u;
+  if (!sh.span) {
+    const uint32_t total = (uint32_t)sh.E * sh.member_words;
+    for (uint32_t x = gtid; x < total; x += gsize) {
+      const int e = x / sh.member_words;
+      const int q = x - e * sh.member_words;
+      if (split_word_is_plain(sh, q))
+        pp.packed[x] = __float_as_uint(split_plain_word(sh, pp.raw + (size_t)e * sh.raw_member_floats, q));
+      else if (q == sh.o_flags)
+        pp.packed[x] = 0u;
     }
   }
-  // header: the idle state every sweep starts from and its last workgroup restores
-  if (gtid == 0) {
-    const int r_bo = sh.raw_member_floats - 1;
-    float bo = 0.0f;
-    for (int e = 0; e < sh.E; ++e) bo += pp.raw[(size_t)e * sh.raw_member_floats + r_bo];
-    pp.hdr->bo_sum = bo;
-    pp.hdr->work_counter = 0u;
-    pp.hdr->n_live = 0u;
-    pp.hdr->done = 0u;
-    pp.hdr->merge_done = 0u;
-    pp.hdr->tau = kKeyMax;
-  }
+  write_tables_and_header(sp, pp, !sh.hoist && !sh.span, gtid, gsize);
 }
 
 // The result of a top-k call over an empty range that merges with nothing: no configuration.
@@ -460,6 +509,7 @@ static int make_shape(const tuner_space* sp, const tuner_model* m, Shape* sh, in
 }
 
 static const Variant* find_variant(const Shape& sh) {
+  if (sh.net == NET_F32_SPLIT) return find_variant_split(sh);
   if (sh.net == NET_F32_MFMA) {
     if (sh.hoist == 2) return find_variant_f32t(sh.NT1, sh.NT2);
     return sh.hoist ? find_variant_f32h(sh.KS, sh.NT1, sh.NT2) : find_variant_f32(sh.KS, sh.NT1, sh.NT2);
@@ -602,6 +652,7 @@ static DeviceInfo device_info_or_default() {
 // LDS bytes of the hoisting networks' per-wave scratch: the high features of a wave's
 // tiles, and for net_f32h.h one z_high vector.
 static int hoist_scratch_bytes(const Shape& sh, const Variant* var) {
+  if (sh.span) return var->waves * sh.rows * (32 + sh.NT1 * 32 + 4) * 4;
   if (!sh.hoist) return 0;
   const int z = sh.hoist == 1 ? std::max(64, sh.NT1 * 32) : 0;
   return var->waves * (var->R * 32 + z) * 4;
@@ -624,12 +675,95 @@ static StagePlan plan_stages(const Shape& sh, const Variant* var, int max_lds) {
   return pl;
 }
 
+static bool is_auto_fp32(const tuner_model* m) { return m->precision == TUNER_FP32 && m->algo == TUNER_ALGO_AUTO; }
+
+// Layout of the two-plane network (net_split.h) on top of the plain fp32 shape `sh`: factored
+// with rows of sp->strides[p0 - 1] configurations (p0 > 0), or behind the fp32 layer 1 that
+// `sh` describes.
+static void make_split_shape(const tuner_space* sp, int p0, Shape* sh) {
+  sh->net = NET_F32_SPLIT;
+  const int units = sh->NT1 * 32, ntl = sh->NT2 ? sh->NT2 : sh->NT1;
+  int at = sh->o_w2;                           // the fp32 layer 1 ends where its layer 2 begins
+  if (p0 > 0) {
+    sh->hoist = 0;
+    sh->p0 = p0;
+    sh->span = (int)sp->strides[p0 - 1];
+    sh->KS = 0;
+    // a wave's two tiles start at a multiple of 32 (the range is extended downwards to one), so
+    // at a multiple of gcd(32, span) in their first row
+    int g = 32;
+    while (sh->span % g) g /= 2;
+    sh->rows = (sh->span - g + 63) / sh->span + 1;
+    if (units == 32) sh->rows = round_up(sh->rows, 2);      // two rows per pass
+    at = sh->span * units;
+  }
+  sh->NPL = 2;
+  sh->o_w1 = 0;
+  sh->o_w2 = at;
+  sh->o_b2 = sh->o_b1 = sh->o_w2 + 2 * sh->NT2 * 2 * sh->NT1 * 256;
+  const int wh_words = sh->hoist ? round_up((sh->p0 + 1) * units, 4) : 0;
+  sh->o_wo = sh->o_b2 + sh->NT2 * 32;
+  sh->o_wh = sh->o_wo + ntl * 32;
+  sh->o_flags = sh->o_wh + (p0 > 0 ? (p0 + 4) / 4 * units * 4 : wh_words);
+  sh->member_words = sh->o_flags + kSplitFlagWords;
+}
+
+// TUNER_ALGO_AUTO, fp32: the two-plane network where it applies.  Range sweeps take the factored
+// first layer when a trailing group of parameters runs through 11 to 128 configurations (fewer
+// would mean more than 7 rows per wave, more a table of over 16 KB per 32 units) and the
+// ensemble then stays resident in LDS with 32 KB left for the candidates, or at least in two
+// stage buffers; of several such groups the one with the fewest passes over the rows, then the
+// smallest table.  One hidden layer in a space of less than 2^18 configurations stays with the
+// fp32 matrix network: its sweep is over before the larger tables pay (131,072 configurations,
+// 11 x 9-30-1, top 200: 41.8 us a call against 43.4; 655,360 x 10-30-1, top 300: 122 against 112).
+// Decided from the space and the model alone, so that tuner_prepare and every later call agree.
+static bool choose_split(const tuner_space* sp, const tuner_model* m, bool range, Shape* sh, const Variant** var) {
+  if (!is_auto_fp32(m)) return false;
+  Shape plain{};
+  if (make_shape(sp, m, &plain, 0) != TUNER_OK) return false;
+  if (!plain.NT2 && sp->n_configs < (1ull << 18)) return false;
+  long best = -1;
+  for (int p0 = plain.P - 1; range && p0 >= 1; --p0) {
+    const uint64_t span = sp->strides[p0 - 1];
+    if (span < 11 || span > (uint64_t)kMaxSpan) continue;
+    Shape s = plain;
+    make_split_shape(sp, p0, &s);
+    const Variant* v = find_variant_split(s);
+    if (!v) continue;
+    const StagePlan pl = plan_stages(s, v, kLdsBytesPerWorkgroup);
+    const int member_bytes = s.member_words * 4;
+    int rank;
+    if (pl.mps >= s.E) rank = (long)s.E * member_bytes + (32 << 10) <= pl.budget ? 0 : 1;
+    else if (pl.double_buffer) rank = 2;
+    else continue;
+    const int passes = s.NT1 == 1 ? s.rows / 2 : s.rows;
+    const long cost = ((long)rank << 40) + ((long)passes << 20) + (long)span;
+    if (best < 0 || cost < best) { best = cost; *sh = s; *var = v; }
+  }
+  if (best >= 0) return true;
+  if (!plain.NT2) return false;                // one hidden layer: the fp32 matrix network
+  Shape s{};
+  if (make_shape(sp, m, &s, range ? 1 : 0) != TUNER_OK) return false;
+  make_split_shape(sp, 0, &s);
+  const Variant* v = find_variant_split(s);
+  if (!v || plan_stages(s, v, kLdsBytesPerWorkgroup).mps < 1) return false;
+  *sh = s;
+  *var = v;
+  return true;
+}
+
 // Shape and kernel variant of a sweep.  Range sweeps (hoist_ok) take the layer-1 shortcuts
 // the space allows; the table of the low parameters' share makes a member larger, so it is
 // used only while the ensemble stays resident in LDS or keeps its two stage buffers.
 static int choose_shape(const tuner_space* sp, const tuner_model* m, bool hoist_ok, int max_lds, Shape* sh,
                         const Variant** var) {
+  {
+    const int rc = make_shape(sp, m, sh, 0);           // argument errors
+    if (rc) return rc;
+  }
+  if (choose_split(sp, m, hoist_ok, sh, var)) return TUNER_OK;
   for (int level = hoist_ok ? 2 : 0; ; --level) {
+    *sh = Shape{};
     const int rc = make_shape(sp, m, sh, level);
     if (rc) return rc;
     *var = find_variant(*sh);
@@ -676,7 +810,12 @@ static int launch_prep(const tuner_space* sp, const tuner_model* m, const Shape&
   pp.hdr = hdr;
   const uint32_t total_packed = (uint32_t)sh.E * sh.member_words;
   const unsigned prep_blocks = std::min<unsigned>(1024, (total_packed + 255) / 256);
-  hipLaunchKernelGGL(prep_kernel, dim3(prep_blocks), dim3(256), 0, stream, sp->dev, pp);
+  if (sh.net == NET_F32_SPLIT) {
+    const unsigned jobs = (unsigned)sh.E * (unsigned)(split_table_slices(sh) + sh.NT2);
+    hipLaunchKernelGGL(prep_split_kernel, dim3(jobs + (sh.span ? 4u : prep_blocks)), dim3(256), 0, stream, sp->dev, pp);
+  } else {
+    hipLaunchKernelGGL(prep_kernel, dim3(prep_blocks), dim3(256), 0, stream, sp->dev, pp);
+  }
   TUNER_HIP_TRY(hipGetLastError());
   return TUNER_OK;
 }
@@ -734,7 +873,7 @@ static int plan_sweep(const tuner_space* sp, const tuner_model* m, uint64_t begi
   // configuration is then evaluated in the same place of the same tile whatever the range,
   // so results do not depend on how a sweep is cut into calls.
   P.head = 0;
-  if (sh.hoist && count > 0) {
+  if ((sh.hoist || sh.span) && count > 0) {
     P.head = (uint32_t)(begin % 32);
     begin -= P.head;
     count += P.head;
@@ -935,7 +1074,16 @@ static int run_sweep(const tuner_space* sp, const tuner_model* m, uint64_t begin
     sw.members_per_stage = P.pl.mps;
     sw.n_stages = (sh.E + P.pl.mps - 1) / P.pl.mps;
     sw.member_words = sh.member_words;
-    sw.off = NetOffsets{sh.o_w1, sh.o_w2, sh.o_b1, sh.o_b2, sh.o_wo, sh.H1, sh.H2, sh.o_wh, sh.p0};
+    sw.off = NetOffsets{};
+    sw.off.w1 = sh.o_w1; sw.off.w2 = sh.o_w2; sw.off.b1 = sh.o_b1; sw.off.b2 = sh.o_b2; sw.off.wo = sh.o_wo;
+    sw.off.h1 = sh.H1; sw.off.h2 = sh.H2; sw.off.wh = sh.o_wh; sw.off.p0 = sh.p0;
+    sw.off.flags = sh.o_flags;
+    if (sh.span) {
+      sw.off.span = (uint32_t)sh.span;
+      sw.off.span_magic = (65536u + (uint32_t)sh.span - 1u) / (uint32_t)sh.span;
+      div_constants((uint32_t)sh.span, &sw.off.span_mul, &sw.off.span_sh);
+      sw.off.rows = (uint32_t)sh.rows;
+    }
     sw.mode = mode;
     sw.merge = merge;
     sw.self_reset = (mode == MODE_ALL && (P.dynamic || P.use_live)) ? 1 : 0;
@@ -1066,6 +1214,12 @@ static int workspace_need(const tuner_space* space, const tuner_model* model, in
     if (!var) return set_error(TUNER_ETOOLARGE, "no kernel variant for this model shape");
     need = std::max(need, tuner::make_layout(sh, k, space->n_configs, var).total);
   }
+  for (int range = 0; range <= 1; ++range) {
+    tuner::Shape sh{};
+    const tuner::Variant* var = nullptr;
+    if (tuner::choose_split(space, model, range != 0, &sh, &var))
+      need = std::max(need, tuner::make_layout(sh, k, space->n_configs, var).total);
+  }
   *need_out = need;
   return TUNER_OK;
 }
@@ -1088,7 +1242,9 @@ int tuner_tabulated_parameters(const tuner_space* space, const tuner_model* mode
   if (!space || !model || !n_tabulated) return set_error(TUNER_EINVAL, "null argument");
   tuner::Shape sh{};
   const tuner::Variant* var = nullptr;
-  const int rc = tuner::choose_shape(space, model, true, tuner::device_info_or_default().max_lds, &sh, &var);
+  tuner_model reported = *model;
+  if (tuner::is_auto_fp32(model)) reported.algo = TUNER_ALGO_MFMA;
+  const int rc = tuner::choose_shape(space, &reported, true, tuner::device_info_or_default().max_lds, &sh, &var);
   if (rc) return rc;
   *n_tabulated = sh.hoist == 2 ? sh.P - sh.p0 : 0;
   return TUNER_OK;
@@ -1104,8 +1260,17 @@ int tuner_sweep_plan(const tuner_space* space, const tuner_model* model, uint64_
                                    k, false, false, tuner::device_info_or_default(), &P);
   if (rc) return rc;
   tuner_sweep_plan_info info{};
-  info.network = P.sh.net;
+  info.network = P.sh.net == tuner::NET_F32_SPLIT ? (int)tuner::NET_F32_MFMA : P.sh.net;
   info.layer1 = P.sh.hoist;
+  if (P.sh.net == tuner::NET_F32_SPLIT) {
+    // the two-plane network reports the layer-1 shortcuts of the fp32 matrix network
+    tuner_model reported = *model;
+    reported.algo = TUNER_ALGO_MFMA;
+    tuner::Shape sh{};
+    const tuner::Variant* var = nullptr;
+    if (tuner::choose_shape(space, &reported, true, tuner::device_info_or_default().max_lds, &sh, &var) == TUNER_OK)
+      info.layer1 = sh.hoist;
+  }
   info.waves = P.var->waves;
   info.tile = P.var->tile;
   info.variant_tiles_per_wave = P.var->R;
