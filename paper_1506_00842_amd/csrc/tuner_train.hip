@@ -113,6 +113,95 @@ sample_compact_kernel(uint64_t seed, uint64_t n_configs, uint32_t max_draws, con
   if (tid == 0) *n_found = (int32_t)found;
 }
 
+// The whole sample in one workgroup, for up to kSmallSample samples: draws are taken in batches of
+// 4 per thread, in draw order, until enough are found, with the table in LDS.  Whether a draw is
+// the first of its index depends on earlier draws only, so nothing past the last sample has to be
+// looked at (a call offers 64 draws per sample, a space with 84 % valid configurations needs 1.2),
+// and a batch costs a microsecond or two instead of a trip to memory per probe.
+// 3,000 of 2,359,296 configurations, 192,000 draws: 504 us with the three kernels above (the last
+// of them one workgroup over all draws), 14.8 us here.
+constexpr uint32_t kSmallSample = 8192;
+constexpr uint32_t kBatchPerThread = 4, kBatch = 1024 * kBatchPerThread;
+
+// LDS table of the single-workgroup sampler: a batch adds at most kBatch entries to fewer than
+// n_samples, and at least a quarter of the slots stays free.
+static uint32_t small_table_slots(uint32_t n_samples) {
+  uint32_t slots = 1024;
+  while (3ull * slots < 4ull * (n_samples + kBatch)) slots <<= 1;
+  return slots;
+}
+
+__global__ void __launch_bounds__(1024)
+sample_small_kernel(const DevSpace space, uint64_t seed, uint64_t n_configs, uint32_t max_draws, uint32_t log_slots,
+                    uint32_t n_samples, uint32_t* __restrict__ out, int32_t* __restrict__ n_found) {
+  extern __shared__ __align__(16) unsigned char sample_smem[];
+  __shared__ uint32_t s_wave[16];
+  DevSpace& sp = *reinterpret_cast<DevSpace*>(sample_smem);
+  unsigned long long* table = reinterpret_cast<unsigned long long*>(sample_smem + (sizeof(DevSpace) + 15) / 16 * 16);
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint32_t slots = 1u << log_slots, mask = slots - 1u;
+  const bool pow2 = space.all_pow2 != 0;
+  for (uint32_t x = tid; x < sizeof(DevSpace) / 4; x += 1024)
+    reinterpret_cast<uint32_t*>(&sp)[x] = reinterpret_cast<const uint32_t*>(&space)[x];
+  for (uint32_t x = tid; x < slots; x += 1024) table[x] = kEmptySlot;
+  __syncthreads();
+  uint32_t found = 0;
+  for (uint64_t base = 0; base < max_draws && found < n_samples; base += kBatch) {
+    uint32_t index[kBatchPerThread], slot[kBatchPerThread];
+    bool entered[kBatchPerThread];
+#pragma unroll
+    for (uint32_t q = 0; q < kBatchPerThread; ++q) {
+      const uint64_t c = base + tid * kBatchPerThread + q;
+      index[q] = draw_index(seed, c, n_configs);
+      entered[q] = c < max_draws && is_valid(sp, index[q], pow2);
+      slot[q] = slot_of(index[q], log_slots);
+      if (!entered[q]) continue;
+      const unsigned long long key = ((unsigned long long)index[q] << 32) | (uint32_t)c;
+      for (uint32_t probe = 0; probe <= mask; ++probe) {
+        unsigned long long cur = table[slot[q]];
+        if (cur == kEmptySlot) {
+          cur = atomicCAS(&table[slot[q]], kEmptySlot, key);
+          if (cur == kEmptySlot) break;
+        }
+        if ((uint32_t)(cur >> 32) == index[q]) {
+          atomicMin(&table[slot[q]], key);
+          break;
+        }
+        slot[q] = (slot[q] + 1u) & mask;
+      }
+    }
+    __syncthreads();
+    // first draws of their index, in draw order
+    uint32_t mine = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kBatchPerThread; ++q) {
+      entered[q] = entered[q] && (uint32_t)table[slot[q]] == (uint32_t)(base + tid * kBatchPerThread + q);
+      mine += entered[q] ? 1u : 0u;
+    }
+    uint32_t upto = mine;                          // inclusive scan over the wave, then over the waves
+    for (uint32_t d = 1; d < 64; d <<= 1) {
+      const uint32_t v = __shfl_up(upto, d);
+      if (lane >= d) upto += v;
+    }
+    if (lane == 63) s_wave[wave] = upto;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+    for (uint32_t w = 0; w < 16; ++w) {
+      if (w < wave) before += s_wave[w];
+      total += s_wave[w];
+    }
+    uint32_t pos = found + before + upto - mine;
+#pragma unroll
+    for (uint32_t q = 0; q < kBatchPerThread; ++q)
+      if (entered[q] && pos < n_samples) out[pos++] = index[q];
+    found += total;
+    __syncthreads();                               // s_wave and the table are read before the next batch writes them
+  }
+  if (found > n_samples) found = n_samples;
+  for (uint32_t x = found + tid; x < n_samples; x += 1024) out[x] = 0xffffffffu;
+  if (tid == 0) *n_found = (int32_t)found;
+}
+
 // ---------------------------------------------------------------------------
 // Training
 // ---------------------------------------------------------------------------
@@ -531,6 +620,16 @@ int tuner_sample_valid(const tuner_space* space, uint64_t seed, uint32_t n_sampl
   const uint32_t n_slots = 1u << log_slots;
   unsigned long long* table = static_cast<unsigned long long*>(workspace_dev);
   const uint32_t md = (uint32_t)max_draws;
+  if (n_samples <= tuner::kSmallSample) {
+    const uint32_t slots = tuner::small_table_slots(n_samples);
+    const size_t lds = (sizeof(tuner::DevSpace) + 15) / 16 * 16 + (size_t)slots * 8;
+    const int rc = tuner::allow_dynamic_lds(reinterpret_cast<const void*>(tuner::sample_small_kernel), (int)lds);
+    if (rc) return rc;
+    hipLaunchKernelGGL(tuner::sample_small_kernel, dim3(1), dim3(1024), lds, stream, space->dev, seed, space->n_configs, md,
+                       tuner::log2_ceil_u64(slots), n_samples, indices_dev, n_found_dev);
+    TUNER_HIP_TRY(hipGetLastError());
+    return TUNER_OK;
+  }
   hipLaunchKernelGGL(tuner::sample_clear_kernel, dim3(std::min<uint32_t>(1024, (n_slots + 255) / 256)), dim3(256), 0,
                      stream, table, n_slots);
   TUNER_HIP_TRY(hipGetLastError());
