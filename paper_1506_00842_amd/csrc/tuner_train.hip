@@ -537,6 +537,24 @@ static const TrainVariant kTrainVariants[] = {
 // ---------------------------------------------------------------------------
 // Metrics
 // ---------------------------------------------------------------------------
+// One workgroup (the entry point has no scratch for more), bound by its CU's vector ALU: 14
+// instructions and 2 transcendentals per value, four 16-byte loads in flight per thread and array
+// where both lists are aligned.  100,003 values: 18 us; 43 us with a load, expf and a division at a
+// time.
+__device__ __forceinline__ void add_relative_error(float y, float t, float& sum, uint32_t& cnt) {
+  // e^y = 2^hi (1 + lo ln 2), hi + lo = y log2 e; (e^y - t) is exact where the two are close
+  const float hi = y * 1.44269504088896340736f;
+  const float lo = fmaf(y, 1.44269504088896340736f, -hi) + y * 1.92596303e-8f;
+  const float p = __builtin_amdgcn_exp2f(hi);
+  const float e = fmaf(p, lo * 0.693147180559945309417f, p);
+  const bool use = usable_time(t) && fabsf(y) < __builtin_inff();
+  float err = fabsf(e - t) * __builtin_amdgcn_rcpf(t);
+  // near the ends of the fp32 range the reciprocal and the exponential lose denormals
+  if (use && !(fabsf(y) < 80.0f && t > 1e-34f && t < 1e34f)) err = fabsf(expf(y) - t) / t;
+  sum += use ? err : 0.0f;
+  cnt += use ? 1u : 0u;
+}
+
 __global__ void __launch_bounds__(1024)
 mean_relative_error_kernel(uint64_t n, const float* __restrict__ pred, const float* __restrict__ times,
                            float* __restrict__ mean_out, int32_t* __restrict__ n_used) {
@@ -545,13 +563,30 @@ mean_relative_error_kernel(uint64_t n, const float* __restrict__ pred, const flo
   const uint32_t tid = threadIdx.x;
   float sum = 0.0f;
   uint32_t cnt = 0;
-  for (uint64_t i = tid; i < n; i += 1024) {
-    const float y = pred[i], t = times[i];
-    if (usable_time(t) && fabsf(y) < __builtin_inff()) {
-      sum += fabsf(expf(y) - t) / t;
-      ++cnt;
+  uint64_t done = 0;
+  if (((reinterpret_cast<uintptr_t>(pred) | reinterpret_cast<uintptr_t>(times)) & 15u) == 0u) {
+    const float4* p4 = reinterpret_cast<const float4*>(pred);
+    const float4* t4 = reinterpret_cast<const float4*>(times);
+    const uint64_t n4 = n / 4;
+    for (uint64_t i = tid; i < n4; i += 4 * 1024) {
+      float4 y[4], t[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint64_t x = i + q * 1024u;
+        y[q] = x < n4 ? p4[x] : make_float4(0.f, 0.f, 0.f, 0.f);
+        t[q] = x < n4 ? t4[x] : make_float4(0.f, 0.f, 0.f, 0.f);      // a failed run: left out
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        add_relative_error(y[q].x, t[q].x, sum, cnt);
+        add_relative_error(y[q].y, t[q].y, sum, cnt);
+        add_relative_error(y[q].z, t[q].z, sum, cnt);
+        add_relative_error(y[q].w, t[q].w, sum, cnt);
+      }
     }
+    done = 4 * n4;
   }
+  for (uint64_t i = done + tid; i < n; i += 1024) add_relative_error(pred[i], times[i], sum, cnt);
   s_sum[tid] = sum;
   s_cnt[tid] = cnt;
   __syncthreads();
