@@ -192,6 +192,87 @@ __device__ __forceinline__ float split_layers(const uint32_t* wm, int lane, cons
   return part;
 }
 
+// The same for two tiles of 32 configurations at once, which share every read of the weights: for
+// second layers of three or four tiles of units, whose accumulators leave room for two waves per
+// SIMD only; the second tile takes the place of the two missing waves.  The weights of one output
+// tile and block are read while the six matrix instructions of the one before run.
+template <int NT1, int NT2, class Tile>
+__device__ __forceinline__ void split_layers_pair(const uint32_t* wm, int lane, const NetOffsets& o, Tile (&tile)[2],
+                                                  float (&out)[2]) {
+  typedef LpNet<_Float16, 2, 1, NT1, NT2, true> Lp;
+  typedef typename Lp::Tr Tr;
+  const int h = lane >> 5;
+  const float4* wo = reinterpret_cast<const float4*>(wm + o.wo);
+  const float4* b2 = reinterpret_cast<const float4*>(wm + o.b2);
+  const uint4* w2 = reinterpret_cast<const uint4*>(wm + o.w2);
+  asm volatile("" ::: "memory");
+  tile[0].load(0);
+  floatx16 a2[2][NT2];
+#pragma unroll
+  for (int u = 0; u < NT2; ++u) {
+    Lp::init_bias(b2, u, h, a2[0][u]);
+    a2[1][u] = a2[0][u];
+  }
+#pragma unroll
+  for (int t = 0; t < NT1; ++t) {
+    B4 hi[2][2], lo[2][2];
+    typename Lp::A4 w_next = Lp::load_w2(w2, t, 0, 0, lane);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      floatx16 a1;
+      tile[c].finish(a1);
+      if (c == 0) tile[1].load(t);
+      split_block(a1, 0, hi[c][0], lo[c][0]);
+      split_block(a1, 1, hi[c][1], lo[c][1]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) asm volatile("" : "+v"(lo[c][b].w[jj]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (t + 1 < NT1) tile[0].load(t + 1);
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int u = 0; u < NT2; ++u) {
+        const typename Lp::A4 w = w_next;
+        const int un = u + 1 < NT2 ? u + 1 : 0, bn = un ? b : b + 1;
+        if (bn < 2) w_next = Lp::load_w2(w2, t, bn, un, lane);
+        const B4 w_hi = {{w.p[0].x, w.p[0].y, w.p[0].z, w.p[0].w}}, w_lo = {{w.p[1].x, w.p[1].y, w.p[1].z, w.p[1].w}};
+        a2[0][u] = Tr::mfma(w_hi, hi[0][b], a2[0][u]);
+        a2[1][u] = Tr::mfma(w_hi, hi[1][b], a2[1][u]);
+        a2[0][u] = Tr::mfma(w_hi, lo[0][b], a2[0][u]);
+        a2[1][u] = Tr::mfma(w_hi, lo[1][b], a2[1][u]);
+        a2[0][u] = Tr::mfma(w_lo, hi[0][b], a2[0][u]);
+        a2[1][u] = Tr::mfma(w_lo, hi[1][b], a2[1][u]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  }
+  float part[2] = {0.0f, 0.0f};
+#pragma unroll
+  for (int u = 0; u < NT2; ++u) {
+    float4 q[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) q[g] = wo[(u * 4 + g) * 2 + h];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      sigmoid16(a2[c][u]);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        part[c] = fmaf(q[g].x, a2[c][u][4 * g + 0], part[c]);
+        part[c] = fmaf(q[g].y, a2[c][u][4 * g + 1], part[c]);
+        part[c] = fmaf(q[g].z, a2[c][u][4 * g + 2], part[c]);
+        part[c] = fmaf(q[g].w, a2[c][u][4 * g + 3], part[c]);
+      }
+      asm volatile("" : "+v"(part[c]));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  out[0] += part[0];
+  out[1] += part[1];
+}
+
 // flag 0 and those of layer 2's tiles
 template <int NT2>
 __device__ __forceinline__ bool split_flags(const uint32_t* wm, const NetOffsets& o) {
@@ -223,11 +304,16 @@ struct SplitNet : L1 {
   }
 };
 
-template <int NT1, int NT2>
+// TABLES_IN_MEMORY: TB and WH stay in memory (a member's are 22 KB and serve from the L1) where the
+// second layer's weights alone fill the two stage buffers: [(t, g)][span][2][4] instead of the
+// swizzled rows, so that the lanes of a wave read side by side.
+template <int NT1, int NT2, bool TABLES_IN_MEMORY = false>
 struct FactoredNet {
   static constexpr int kTile = 32;
   static constexpr bool kHoist = false;
   static constexpr bool kRows = true;
+  static constexpr bool kPair = NT2 >= 3;
+  static constexpr bool kTablesInMemory = TABLES_IN_MEMORY;
   static constexpr int kUnits = NT1 * 32;
   static constexpr int kRowFloats = kUnits + 4;   // scratch row (rows are read side by side: 4 floats apart in the banks)
   struct Feat { uint32_t tb, zs; };               // byte offsets of the lane's place in TB and of its row in the scratch
@@ -236,7 +322,7 @@ struct FactoredNet {
   static __device__ __forceinline__ void place(uint32_t at, int lane, const NetOffsets& o, Feat& f) {
     const uint32_t h = (uint32_t)lane >> 5;
     const uint32_t row = (at * o.span_magic) >> 16, lo = at - row * o.span;
-    f.tb = lo * (kUnits * 4u) + ((h ^ (lo & 7u)) << 4);
+    f.tb = TABLES_IN_MEMORY ? lo * 32u + (h << 4) : lo * (kUnits * 4u) + ((h ^ (lo & 7u)) << 4);
     f.zs = row * (kRowFloats * 4u) + (h << 4);
   }
 
@@ -253,15 +339,16 @@ struct FactoredNet {
   }
 
   // Once per member: 2^z_row[u] (or z_row[u], flag 0) of every unit for the wave's rows
-  static __device__ __forceinline__ void rows(const uint32_t* wm, uint32_t n_rows, int lane, const NetOffsets& o,
-                                              const float* xs, float* zs) {
+  // (`tables`: the member's TB and WH, in memory or in LDS like the rest of it)
+  static __device__ __forceinline__ void rows(const uint32_t* wm, const uint32_t* tables, uint32_t n_rows, int lane,
+                                              const NetOffsets& o, const float* xs, float* zs) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    const float4* wh = reinterpret_cast<const float4*>(wm + o.wh);
+    const float4* wh = reinterpret_cast<const float4*>(tables + o.wh);
     const float4* x4 = reinterpret_cast<const float4*>(xs);
     const bool plain = __builtin_amdgcn_readfirstlane(wm[o.flags]) != 0u;
     const int groups = (o.p0 + 4) >> 2;
-    constexpr int kPer = kUnits > 64 ? kUnits / 64 : 1;       // units per lane
+    constexpr int kPer = (kUnits + 63) / 64;                  // units per lane
     constexpr uint32_t kStep = kUnits == 32 ? 2u : 1u;        // rows per pass
     const uint32_t r_lane = kUnits == 32 ? (uint32_t)lane >> 5 : 0u;
     const int u = kUnits == 32 ? (lane & 31) : lane;
@@ -274,7 +361,7 @@ struct FactoredNet {
         const float4 x = x4[r * 8 + g];
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
-          const float4 w = wh[g * kUnits + u + 64 * q];
+          const float4 w = wh[g * kUnits + (kUnits == 96 && q ? 64 + (u & 31) : u + 64 * q)];
           z[q] = fmaf(w.x, x.x, z[q]);
           z[q] = fmaf(w.y, x.y, z[q]);
           z[q] = fmaf(w.z, x.z, z[q]);
@@ -282,7 +369,8 @@ struct FactoredNet {
         }
       }
 #pragma unroll
-      for (int q = 0; q < kPer; ++q) zs[r * kRowFloats + u + 64 * q] = plain ? z[q] : __builtin_amdgcn_exp2f(z[q]);
+      for (int q = 0; q < kPer; ++q)
+        zs[r * kRowFloats + (kUnits == 96 && q ? 64 + (u & 31) : u + 64 * q)] = plain ? z[q] : __builtin_amdgcn_exp2f(z[q]);
     }
     // a wave's LDS instructions execute in program order; the fences keep the compiler from
     // moving the reads of forward() above these writes, or the next member's writes above them
@@ -291,55 +379,76 @@ struct FactoredNet {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
 
-  static __device__ __forceinline__ float forward(const uint32_t* wm, const Feat& f, int lane,
+  static __device__ __forceinline__ float forward(const uint32_t* wm, const uint32_t* tables, const Feat& f, int lane,
                                                   const NetOffsets& o, const float* zs) {
-    if (split_flags<NT2>(wm, o)) return forward_t<true>(wm, f, lane, o, zs);
-    return forward_t<false>(wm, f, lane, o, zs);
+    if (split_flags<NT2>(wm, o)) return forward_t<true>(wm, tables, f, lane, o, zs);
+    return forward_t<false>(wm, tables, f, lane, o, zs);
+  }
+  // two tiles at once (kPair): the sums are added to y
+  static __device__ __forceinline__ void forward_pair(const uint32_t* wm, const uint32_t* tables, const Feat (&f)[2], int lane,
+                                                      const NetOffsets& o, const float* zs, float (&y)[2]) {
+    if (split_flags<NT2>(wm, o)) {
+      for (int c = 0; c < 2; ++c) y[c] += forward_t<true>(wm, tables, c ? f[1] : f[0], lane, o, zs);
+      return;
+    }
+    Tile<false> tile[2];
+    tile[0].init(wm, tables, f[0], o, zs);
+    tile[1].init(wm, tables, f[1], o, zs);
+    split_layers_pair<NT1, NT2>(wm, lane, o, tile, y);
   }
   // FLAGS: exponents in the tables or fp32 tiles in layer 2, as the member's flags say
   template <bool FLAGS>
-  static __device__ __forceinline__ float forward_t(const uint32_t* wm, const Feat& f, int lane,
+  static __device__ __forceinline__ float forward_t(const uint32_t* wm, const uint32_t* tables, const Feat& f, int lane,
                                                     const NetOffsets& o, const float* zs) {
-    struct Tile {
-      const char *tb, *zb;
-      uint32_t at, exponents;
-      float4 eh[4], el[4];
-      __device__ __forceinline__ void load(int t) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          el[g] = *reinterpret_cast<const float4*>(tb + (at ^ (uint32_t)(g << 5)) + t * 128);
-          eh[g] = *reinterpret_cast<const float4*>(zb + t * 128 + g * 32);
-        }
-      }
-      // 1 + 2^z, then the reciprocals
-      __device__ __forceinline__ void finish(floatx16& a) {
-        if (FLAGS && exponents) {
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            a[4 * g + 0] = 1.0f + __builtin_amdgcn_exp2f(eh[g].x + el[g].x);
-            a[4 * g + 1] = 1.0f + __builtin_amdgcn_exp2f(eh[g].y + el[g].y);
-            a[4 * g + 2] = 1.0f + __builtin_amdgcn_exp2f(eh[g].z + el[g].z);
-            a[4 * g + 3] = 1.0f + __builtin_amdgcn_exp2f(eh[g].w + el[g].w);
-          }
-        } else {
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            a[4 * g + 0] = fmaf(eh[g].x, el[g].x, 1.0f);
-            a[4 * g + 1] = fmaf(eh[g].y, el[g].y, 1.0f);
-            a[4 * g + 2] = fmaf(eh[g].z, el[g].z, 1.0f);
-            a[4 * g + 3] = fmaf(eh[g].w, el[g].w, 1.0f);
-          }
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) a[v] = __builtin_amdgcn_rcpf(a[v]);
-      }
-    } tile;
-    tile.tb = reinterpret_cast<const char*>(wm + o.w1);
-    tile.zb = reinterpret_cast<const char*>(zs) + f.zs;
-    tile.at = f.tb;
-    tile.exponents = FLAGS ? (uint32_t)__builtin_amdgcn_readfirstlane(wm[o.flags]) : 0u;
+    Tile<FLAGS> tile;
+    tile.init(wm, tables, f, o, zs);
     return split_layers<NT1, NT2, FLAGS>(wm, lane, o, tile);
   }
+
+  template <bool FLAGS>
+  struct Tile {
+    const char *tb, *zb;
+    uint32_t at, exponents, step;
+    float4 eh[4], el[4];
+    __device__ __forceinline__ void init(const uint32_t* wm, const uint32_t* tables, const Feat& f, const NetOffsets& o,
+                                         const float* zs) {
+      tb = reinterpret_cast<const char*>(tables + o.w1);
+      zb = reinterpret_cast<const char*>(zs) + f.zs;
+      at = f.tb;
+      step = o.span * 32u;
+      exponents = FLAGS ? (uint32_t)__builtin_amdgcn_readfirstlane(wm[o.flags]) : 0u;
+    }
+    __device__ __forceinline__ void load(int t) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        if constexpr (TABLES_IN_MEMORY) el[g] = *reinterpret_cast<const float4*>(tb + (uint32_t)(t * 4 + g) * step + at);
+        else el[g] = *reinterpret_cast<const float4*>(tb + (at ^ (uint32_t)(g << 5)) + t * 128);
+        eh[g] = *reinterpret_cast<const float4*>(zb + t * 128 + g * 32);
+      }
+    }
+    // 1 + 2^z, then the reciprocals
+    __device__ __forceinline__ void finish(floatx16& a) {
+      if (FLAGS && exponents) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          a[4 * g + 0] = 1.0f + __builtin_amdgcn_exp2f(eh[g].x + el[g].x);
+          a[4 * g + 1] = 1.0f + __builtin_amdgcn_exp2f(eh[g].y + el[g].y);
+          a[4 * g + 2] = 1.0f + __builtin_amdgcn_exp2f(eh[g].z + el[g].z);
+          a[4 * g + 3] = 1.0f + __builtin_amdgcn_exp2f(eh[g].w + el[g].w);
+        }
+      } else {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          a[4 * g + 0] = fmaf(eh[g].x, el[g].x, 1.0f);
+          a[4 * g + 1] = fmaf(eh[g].y, el[g].y, 1.0f);
+          a[4 * g + 2] = fmaf(eh[g].z, el[g].z, 1.0f);
+          a[4 * g + 3] = fmaf(eh[g].w, el[g].w, 1.0f);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) a[v] = __builtin_amdgcn_rcpf(a[v]);
+    }
+  };
 };
 
 // ---- packing --------------------------------------------------------------------------------
@@ -388,8 +497,9 @@ __host__ __device__ inline int split_table_slices(const Shape& sh) {
 
 // A workgroup of 256 threads writes one slice of TB of one member (factored layout), the first
 // one also WH, b2A, woA and flag 0.  Everything is read into LDS first, in one trip to memory.
-__device__ inline void pack_factored(const Shape& sh, const float* raw, uint32_t* member, const DevSpace& sp, int slice,
-                                     PackScratch& s) {
+// `tables`: where the member's TB and WH go (the member itself, or its place behind all members).
+__device__ inline void pack_factored(const Shape& sh, const float* raw, uint32_t* member, uint32_t* tables, const DevSpace& sp,
+                                     int slice, PackScratch& s) {
   const int tid = threadIdx.x, units = sh.NT1 * 32, n_low = sh.P - sh.p0;
   const bool pow2 = sp.all_pow2 != 0;
   if (tid == 0) s.any = 0u;
@@ -415,7 +525,9 @@ __device__ inline void pack_factored(const Shape& sh, const float* raw, uint32_t
       for (int p = 0; p < n_low; ++p) z = fma((double)s.w[u * sh.P + sh.p0 + p], (double)s.x[l * n_low + p], z);
     z *= kNegLog2eD;
     const int t = u >> 5, e = (u >> 2) & 7, j = u & 3;
-    member[l * units + 32 * t + 4 * (e ^ (l & 7)) + j] = __float_as_uint(plain ? (float)z : exp2_of(z));
+    const int at = sh.table_words ? ((t * 4 + (e >> 1)) * sh.span + l) * 8 + (e & 1) * 4 + j
+                                  : l * units + 32 * t + 4 * (e ^ (l & 7)) + j;
+    tables[at] = __float_as_uint(plain ? (float)z : exp2_of(z));
   }
   if (slice != 0) return;
   if (tid == 0) member[sh.o_flags] = plain ? 1u : 0u;
@@ -424,7 +536,7 @@ __device__ inline void pack_factored(const Shape& sh, const float* raw, uint32_t
     const int j = x & 3, u = (x >> 2) % units, p = 4 * ((x >> 2) / units) + j;
     float v = 0.0f;
     if (u < sh.H1 && p <= sh.p0) v = (float)((double)(p < sh.p0 ? s.w[u * sh.P + p] : b1[u]) * kNegLog2eD);
-    member[sh.o_wh + x] = __float_as_uint(v);
+    tables[sh.o_wh + x] = __float_as_uint(v);
   }
   for (int x = tid; x < sh.NT2 * 32; x += 256) {
     // accumulator order [4][2][4]: word 8 g + 4 h + j of a tile is its unit 8 g + 4 h + j

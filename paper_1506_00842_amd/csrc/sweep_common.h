@@ -53,6 +53,7 @@ struct Shape {
   int o_flags;
   int span;                   // > 0: factored first layer; configurations per row
   int rows;                   // ... and the most rows a wave's tiles reach
+  int table_words;            // > 0: TB and WH stay in memory, behind all members, in this many words each
 };
 
 struct NetOffsets {
@@ -61,6 +62,7 @@ struct NetOffsets {
   uint32_t span, span_magic;                   // factored first layer: span; ceil(2^16 / span) divides places < 256
   uint32_t span_mul, span_sh;                  // division constants of the span (fast_div)
   uint32_t rows;                               // rows of the per-wave scratch
+  int table_words;                             // tables in memory: words per member
 };
 
 struct SweepParams {

@@ -302,12 +302,25 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
       for (int m = 0; m < nm; ++m) {
         const uint32_t* w = stage + (size_t)m * prm.member_words;
         if constexpr (Net::kRows) {
-          if (any_tile) Net::rows(w, n_rows, lane, prm.off, hoist_xs, hoist_zs);
+          const uint32_t* tables = w;
+          if constexpr (Net::kTablesInMemory)
+            tables = prm.packed + (size_t)prm.n_members * prm.member_words + (size_t)(first + m) * prm.off.table_words;
+          if (any_tile) Net::rows(w, tables, n_rows, lane, prm.off, hoist_xs, hoist_zs);
+          if constexpr (Net::kPair && R == 2) {
+            if (any[0] && any[1]) {
+              Net::forward_pair(w, tables, feat, lane, prm.off, hoist_zs, ysum);
+              continue;
+            }
+          }
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            if (any[r]) ysum[r] += Net::forward(w, tables, feat[r], lane, prm.off, hoist_zs);
+          continue;
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           if (any[r]) {
-            if constexpr (Net::kRows) ysum[r] += Net::forward(w, feat[r], lane, prm.off, hoist_zs);
+            if constexpr (Net::kRows) {}                 // done above
             else if constexpr (Net::kHoist) ysum[r] += Net::forward(w, feat[r], lane, prm.off, hoist_xs + r * 32, hoist_zs);
             else ysum[r] += Net::forward(w, feat[r], lane, prm.off);
           }

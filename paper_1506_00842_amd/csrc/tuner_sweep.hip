@@ -114,8 +114,9 @@ __global__ void __launch_bounds__(256) prep_split_kernel(const DevSpace sp, cons
   uint32_t b = blockIdx.x;
   if (b < n_tables) {
     const uint32_t e = b / slices;
-    pack_factored(sh, pp.raw + (size_t)e * sh.raw_member_floats, pp.packed + (size_t)e * sh.member_words, sp,
-                  (int)(b - e * slices), scratch);
+    uint32_t* member = pp.packed + (size_t)e * sh.member_words;
+    uint32_t* tables = sh.table_words ? pp.packed + (size_t)sh.E * sh.member_words + (size_t)e * sh.table_words : member;
+    pack_factored(sh, pp.raw + (size_t)e * sh.raw_member_floats, member, tables, sp, (int)(b - e * slices), scratch);
     return;
   }
   b -= n_tables;
@@ -600,7 +601,7 @@ static Layout make_layout(const Shape& sh, int k, uint64_t n_configs, const Vari
   L.o_hdr = 0;
   L.o_space = al(sizeof(WsHeader));
   L.o_packed = L.o_space + kSpaceBytes;
-  L.o_pools = L.o_packed + al((size_t)sh.E * sh.member_words * 4);
+  L.o_pools = L.o_packed + al((size_t)sh.E * (sh.member_words + sh.table_words) * 4);
   L.kp = k > 0 ? host_next_pow2((uint32_t)k) : 0;
   const uint32_t unit_max = (uint32_t)(kMaxIter * kMaxSuper);
   L.cap = k > 0 ? 4u * (L.kp > unit_max ? L.kp : unit_max) : 0;
@@ -680,8 +681,13 @@ static bool is_auto_fp32(const tuner_model* m) { return m->precision == TUNER_FP
 // Layout of the two-plane network (net_split.h) on top of the plain fp32 shape `sh`: factored
 // with rows of sp->strides[p0 - 1] configurations (p0 > 0), or behind the fp32 layer 1 that
 // `sh` describes.
-static void make_split_shape(const tuner_space* sp, int p0, Shape* sh) {
+static void make_split_shape(const tuner_space* sp, int p0, bool tables_in_memory, Shape* sh) {
   sh->net = NET_F32_SPLIT;
+  if (p0 > 0) {
+    // any pair of tile counts has its kernel
+    sh->NT1 = (sh->H1 + 31) / 32;
+    sh->NT2 = (sh->H2 + 31) / 32;
+  }
   const int units = sh->NT1 * 32, ntl = sh->NT2 ? sh->NT2 : sh->NT1;
   int at = sh->o_w2;                           // the fp32 layer 1 ends where its layer 2 begins
   if (p0 > 0) {
@@ -695,7 +701,7 @@ static void make_split_shape(const tuner_space* sp, int p0, Shape* sh) {
     while (sh->span % g) g /= 2;
     sh->rows = (sh->span - g + 63) / sh->span + 1;
     if (units == 32) sh->rows = round_up(sh->rows, 2);      // two rows per pass
-    at = sh->span * units;
+    at = tables_in_memory ? 0 : sh->span * units;
   }
   sh->NPL = 2;
   sh->o_w1 = 0;
@@ -704,15 +710,20 @@ static void make_split_shape(const tuner_space* sp, int p0, Shape* sh) {
   const int wh_words = sh->hoist ? round_up((sh->p0 + 1) * units, 4) : 0;
   sh->o_wo = sh->o_b2 + sh->NT2 * 32;
   sh->o_wh = sh->o_wo + ntl * 32;
-  sh->o_flags = sh->o_wh + (p0 > 0 ? (p0 + 4) / 4 * units * 4 : wh_words);
+  const int factored_wh = p0 > 0 ? (p0 + 4) / 4 * units * 4 : 0;
+  sh->o_flags = sh->o_wh + (tables_in_memory ? 0 : p0 > 0 ? factored_wh : wh_words);
   sh->member_words = sh->o_flags + kSplitFlagWords;
+  if (tables_in_memory) {
+    sh->o_wh = sh->span * units;               // in the member's tables
+    sh->table_words = sh->o_wh + factored_wh;
+  }
 }
 
 // TUNER_ALGO_AUTO, fp32: the two-plane network where it applies.  Range sweeps take the factored
 // first layer when a trailing group of parameters runs through 11 to 128 configurations (fewer
 // would mean more than 7 rows per wave, more a table of over 16 KB per 32 units) and the
 // ensemble then stays resident in LDS with 32 KB left for the candidates, or at least in two
-// stage buffers; of several such groups the one with the fewest passes over the rows, then the
+// stage buffers, if need be with the first layer's tables left in memory; of several such groups the one with the fewest passes over the rows, then the
 // smallest table.  One hidden layer in a space of less than 2^18 configurations stays with the
 // fp32 matrix network: its sweep is over before the larger tables pay (131,072 configurations,
 // 11 x 9-30-1, top 200: 41.8 us a call against 43.4; 655,360 x 10-30-1, top 300: 122 against 112).
@@ -723,11 +734,17 @@ static bool choose_split(const tuner_space* sp, const tuner_model* m, bool range
   if (make_shape(sp, m, &plain, 0) != TUNER_OK) return false;
   if (!plain.NT2 && sp->n_configs < (1ull << 18)) return false;
   long best = -1;
-  for (int p0 = plain.P - 1; range && p0 >= 1; --p0) {
+  for (int p0 = plain.P - 1, in_memory = 0; range && in_memory <= 1; --p0) {
+    if (p0 < 1) {                              // next the tables in memory, if nothing fits with them in LDS
+      if (best >= 0 || !plain.NT2) break;
+      ++in_memory;
+      p0 = plain.P;
+      continue;
+    }
     const uint64_t span = sp->strides[p0 - 1];
     if (span < 11 || span > (uint64_t)kMaxSpan) continue;
     Shape s = plain;
-    make_split_shape(sp, p0, &s);
+    make_split_shape(sp, p0, in_memory != 0, &s);
     const Variant* v = find_variant_split(s);
     if (!v) continue;
     const StagePlan pl = plan_stages(s, v, kLdsBytesPerWorkgroup);
@@ -744,7 +761,7 @@ static bool choose_split(const tuner_space* sp, const tuner_model* m, bool range
   if (!plain.NT2) return false;                // one hidden layer: the fp32 matrix network
   Shape s{};
   if (make_shape(sp, m, &s, range ? 1 : 0) != TUNER_OK) return false;
-  make_split_shape(sp, 0, &s);
+  make_split_shape(sp, 0, false, &s);
   const Variant* v = find_variant_split(s);
   if (!v || plan_stages(s, v, kLdsBytesPerWorkgroup).mps < 1) return false;
   *sh = s;
@@ -1083,6 +1100,7 @@ static int run_sweep(const tuner_space* sp, const tuner_model* m, uint64_t begin
       sw.off.span_magic = (65536u + (uint32_t)sh.span - 1u) / (uint32_t)sh.span;
       div_constants((uint32_t)sh.span, &sw.off.span_mul, &sw.off.span_sh);
       sw.off.rows = (uint32_t)sh.rows;
+      sw.off.table_words = sh.table_words;
     }
     sw.mode = mode;
     sw.merge = merge;

@@ -40,7 +40,7 @@ def predict(sp, m, begin, count, **kw):
     ((16, 8, 4, 4), (2, 2, 2, 2, 2)), ((6, 5, 4, 3, 3), (5, 7)), ((12, 8, 6), (3, 16)), ((5, 8, 8), (2, 1, 37)),
     ((200, 9), (13,)), ((4, 4, 4, 4, 4, 4, 4, 4), (2, 2)),
 ])
-@pytest.mark.parametrize("hidden", [[1, 1], [33, 31], [64, 65], [128, 17]])
+@pytest.mark.parametrize("hidden", [[1, 1], [33, 31], [64, 65], [128, 17], [96, 97], [20, 128], [128, 128]])
 def test_spans_and_widths(lead, tail, hidden):
     sp = space_with_tail(lead, tail)
     n = sp.n_configs
@@ -56,7 +56,7 @@ def test_spans_and_widths(lead, tail, hidden):
     assert np.array_equal(part.view(np.int32), whole[n // 3 + 1:n // 3 + 1 + len(part)].view(np.int32))
 
 
-@pytest.mark.parametrize("hidden", [16, 30, 64, 100])
+@pytest.mark.parametrize("hidden", [16, 30, 64, 80, 100])
 def test_one_hidden_layer(hidden):
     sp = space_with_tail((8, 8, 8, 8, 5), (2, 2, 3, 3))          # 737,280 configurations: factored
     m = wl.make_model([sp.n_params, hidden, 1], 11, hidden)
@@ -95,13 +95,14 @@ def scale_weights(m, kind):
 
 
 @pytest.mark.parametrize("kind", ["large-w2", "small-w2", "mixed-rows", "large-bias", "zero-rows", "large-w1", "huge"])
-@pytest.mark.parametrize("lead,tail", [((8, 7, 6, 5), (2, 2, 2, 2, 2)), ((64, 8), (5,))])
-def test_magnitudes_of_weights(kind, lead, tail):
+@pytest.mark.parametrize("lead,tail,hidden", [((8, 7, 6, 5), (2, 2, 2, 2, 2), [48, 40]), ((64, 8), (5,), [48, 40]),
+                                              ((8, 7, 6, 5), (2, 2, 2, 2, 2), [128, 120])])
+def test_magnitudes_of_weights(kind, lead, tail, hidden):
     """Weights of unusual magnitude: the error against the oracle, in the 2-norm over the
     configurations, stays within twice that of the fp32 instructions (weights beyond 64 use them)
     plus the fp32 rounding of the result, 1e-6 of the predictions' scale."""
     sp = space_with_tail(lead, tail, n_rules=0)
-    m = wl.make_model([sp.n_params, 48, 40, 1], 2, 5)
+    m = wl.make_model([sp.n_params, *hidden, 1], 2, 5)
     scale_weights(m, kind)
     import paper_1506_00842_amd as T
     n = sp.n_configs
