@@ -58,13 +58,15 @@ __device__ __forceinline__ uint32_t split_remainders(float a, float b, uint32_t 
   asm("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(lo) : "v"(hi), "v"(b));
   return lo;
 }
+// pair jj of block b of a tile's sigmoid values
+__device__ __forceinline__ void split_pair(const floatx16& a, int b, int jj, B4& hi, B4& lo) {
+  const float2v ab = {a[8 * b + 2 * jj], a[8 * b + 2 * jj + 1]};
+  hi.w[jj] = __builtin_bit_cast(uint32_t, __builtin_convertvector(ab, f16x2));
+  lo.w[jj] = split_remainders(ab.x, ab.y, hi.w[jj]);
+}
 __device__ __forceinline__ void split_block(const floatx16& a, int b, B4& hi, B4& lo) {
 #pragma unroll
-  for (int jj = 0; jj < 4; ++jj) {
-    const float2v ab = {a[8 * b + 2 * jj], a[8 * b + 2 * jj + 1]};
-    hi.w[jj] = __builtin_bit_cast(uint32_t, __builtin_convertvector(ab, f16x2));
-    lo.w[jj] = split_remainders(ab.x, ab.y, hi.w[jj]);
-  }
+  for (int jj = 0; jj < 4; ++jj) split_pair(a, b, jj, hi, lo);
 }
 
 // Layer 2 and the output from the sigmoid values of layer 1, which `tile` produces for the
@@ -192,10 +194,12 @@ __device__ __forceinline__ float split_layers(const uint32_t* wm, int lane, cons
   return part;
 }
 
-// The same for two tiles of 32 configurations at once, which share every read of the weights: for
-// second layers of three or four tiles of units, whose accumulators leave room for two waves per
-// SIMD only; the second tile takes the place of the two missing waves.  The weights of one output
-// tile and block are read while the six matrix instructions of the one before run.
+// The same for two tiles of 32 configurations at once: for second layers of three or four tiles of
+// units, whose accumulators leave room for two waves per SIMD only.  Two waves do not keep the
+// matrix cores and the vector ALU busy side by side by themselves (MFMA 0.40 and VALU 0.52 of the
+// cycles, in turn), so the order inside the wave does: while the matrix instructions of one tile
+// of configurations and 32 inputs run, the sigmoids of the other tile's (or the next) 32 inputs are
+// formed and split, a few vector instructions behind each matrix instruction.
 template <int NT1, int NT2, class Tile>
 __device__ __forceinline__ void split_layers_pair(const uint32_t* wm, int lane, const NetOffsets& o, Tile (&tile)[2],
                                                   float (&out)[2]) {
@@ -213,40 +217,67 @@ __device__ __forceinline__ void split_layers_pair(const uint32_t* wm, int lane, 
     Lp::init_bias(b2, u, h, a2[0][u]);
     a2[1][u] = a2[0][u];
   }
+  B4 hi[2][2], lo[2][2];                   // [tile of configurations][block of 16 inputs]
+  floatx16 a1;
+  // piece k = 0 .. 19 of forming and splitting 32 sigmoid values of tile c
+  auto piece = [&](int k, int c) {
+    if (k < 4) {
+      tile[c].sums(a1, k);
 #pragma unroll
-  for (int t = 0; t < NT1; ++t) {
-    B4 hi[2][2], lo[2][2];
-    typename Lp::A4 w_next = Lp::load_w2(w2, t, 0, 0, lane);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      floatx16 a1;
-      tile[c].finish(a1);
-      if (c == 0) tile[1].load(t);
-      split_block(a1, 0, hi[c][0], lo[c][0]);
-      split_block(a1, 1, hi[c][1], lo[c][1]);
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) asm volatile("" : "+v"(lo[c][b].w[jj]));
-      __builtin_amdgcn_sched_barrier(0);
+      for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(a1[4 * k + j]));
+    } else if (k < 12) {
+      const int v = 2 * (k - 4);
+      a1[v] = __builtin_amdgcn_rcpf(a1[v]);
+      a1[v + 1] = __builtin_amdgcn_rcpf(a1[v + 1]);
+      asm volatile("" : "+v"(a1[v]), "+v"(a1[v + 1]));
+    } else {
+      const int b = (k - 12) / 4, jj = (k - 12) % 4;
+      split_pair(a1, b, jj, hi[c][b], lo[c][b]);
+      asm volatile("" : "+v"(lo[c][b].w[jj]));
     }
-    if (t + 1 < NT1) tile[0].load(t + 1);
+  };
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < 20; ++k) piece(k, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  constexpr int kSteps = 2 * NT1, kMatrix = 6 * NT2;
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    const int c = s & 1, t = s >> 1, cn = 1 - c, tn = (s + 1) >> 1;
+    // first the next step's table reads, then this step's first weights
+    if (s + 1 < kSteps) tile[cn].load(tn);
+    typename Lp::A4 w[2], w_next[2];
+    w_next[0] = Lp::load_w2(w2, t, 0, 0, lane);
+    w_next[1] = Lp::load_w2(w2, t, 0, 1, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    int i = 0;
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int u = 0; u < NT2; ++u) {
-        const typename Lp::A4 w = w_next;
-        const int un = u + 1 < NT2 ? u + 1 : 0, bn = un ? b : b + 1;
-        if (bn < 2) w_next = Lp::load_w2(w2, t, bn, un, lane);
-        const B4 w_hi = {{w.p[0].x, w.p[0].y, w.p[0].z, w.p[0].w}}, w_lo = {{w.p[1].x, w.p[1].y, w.p[1].z, w.p[1].w}};
-        a2[0][u] = Tr::mfma(w_hi, hi[0][b], a2[0][u]);
-        a2[1][u] = Tr::mfma(w_hi, hi[1][b], a2[1][u]);
-        a2[0][u] = Tr::mfma(w_hi, lo[0][b], a2[0][u]);
-        a2[1][u] = Tr::mfma(w_hi, lo[1][b], a2[1][u]);
-        a2[0][u] = Tr::mfma(w_lo, hi[0][b], a2[0][u]);
-        a2[1][u] = Tr::mfma(w_lo, hi[1][b], a2[1][u]);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int u0 = 0; u0 < NT2; u0 += 2) {
+        w[0] = w_next[0];
+        w[1] = w_next[1];
+        const int un = u0 + 2 < NT2 ? u0 + 2 : 0, bn = un ? b : b + 1;
+        if (bn < 2) {
+          w_next[0] = Lp::load_w2(w2, t, bn, un, lane);
+          if (un + 1 < NT2) w_next[1] = Lp::load_w2(w2, t, bn, un + 1, lane);
+        }
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+          for (int d = 0; d < 2; ++d) {
+            if (u0 + d >= NT2) continue;
+            const uint4 q = w[d].p[p < 2 ? 0 : 1];
+            a2[c][u0 + d] = Tr::mfma(B4{{q.x, q.y, q.z, q.w}}, p == 1 ? lo[c][b] : hi[c][b], a2[c][u0 + d]);
+            // pieces from the third instruction on: the table reads have arrived by then
+            if (s + 1 < kSteps) {
+#pragma unroll
+              for (int k = 0; k < 20; ++k)
+                if (2 + k * (kMatrix - 2) / 20 == i) piece(k, cn);
+            }
+            ++i;
+            __builtin_amdgcn_sched_barrier(0);
+          }
       }
   }
   float part[2] = {0.0f, 0.0f};
@@ -426,7 +457,13 @@ struct FactoredNet {
         eh[g] = *reinterpret_cast<const float4*>(zb + t * 128 + g * 32);
       }
     }
-    // 1 + 2^z, then the reciprocals
+    // 1 + 2^z of units 4 g + j
+    __device__ __forceinline__ void sums(floatx16& a, int g) {
+      a[4 * g + 0] = fmaf(eh[g].x, el[g].x, 1.0f);
+      a[4 * g + 1] = fmaf(eh[g].y, el[g].y, 1.0f);
+      a[4 * g + 2] = fmaf(eh[g].z, el[g].z, 1.0f);
+      a[4 * g + 3] = fmaf(eh[g].w, el[g].w, 1.0f);
+    }
     __device__ __forceinline__ void finish(floatx16& a) {
       if (FLAGS && exponents) {
 #pragma unroll
@@ -438,12 +475,7 @@ struct FactoredNet {
         }
       } else {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          a[4 * g + 0] = fmaf(eh[g].x, el[g].x, 1.0f);
-          a[4 * g + 1] = fmaf(eh[g].y, el[g].y, 1.0f);
-          a[4 * g + 2] = fmaf(eh[g].z, el[g].z, 1.0f);
-          a[4 * g + 3] = fmaf(eh[g].w, el[g].w, 1.0f);
-        }
+        for (int g = 0; g < 4; ++g) sums(a, g);
       }
 #pragma unroll
       for (int v = 0; v < 16; ++v) a[v] = __builtin_amdgcn_rcpf(a[v]);
