@@ -335,33 +335,50 @@ struct SplitNet : L1 {
   }
 };
 
+// ROWS_SHARED (one hidden layer, resident ensemble): the rows of a whole chunk are computed by the
+// workgroup for all members before the chunk is evaluated, instead of by every wave for its own
+// tiles, member by member.  A wave's pass over its rows is a chain of LDS reads, sums, an
+// exponential and a write before the member can begin; with one tile per wave it cost more than
+// the member (655,360 configurations, 11 x 10-30-1, all predictions: 72 us, shared 57; with two
+// tiles per wave a pass serves both: 2,359,296 x 11-30-1 155 us, shared 162).
 // TABLES_IN_MEMORY: TB and WH stay in memory (a member's are 22 KB and serve from the L1) where the
 // second layer's weights alone fill the two stage buffers: [(t, g)][span][2][4] instead of the
 // swizzled rows, so that the lanes of a wave read side by side.
-template <int NT1, int NT2, bool TABLES_IN_MEMORY = false>
+template <int NT1, int NT2, bool TABLES_IN_MEMORY = false, bool ROWS_SHARED = false>
 struct FactoredNet {
   static constexpr int kTile = 32;
   static constexpr bool kHoist = false;
   static constexpr bool kRows = true;
+  static constexpr bool kRowsShared = ROWS_SHARED;
   static constexpr bool kPair = NT2 >= 3;
   static constexpr bool kTablesInMemory = TABLES_IN_MEMORY;
   static constexpr int kUnits = NT1 * 32;
   static constexpr int kRowFloats = kUnits + 4;   // scratch row (rows are read side by side: 4 floats apart in the banks)
   struct Feat { uint32_t tb, zs; };               // byte offsets of the lane's place in TB and of its row in the scratch
 
-  // `at` = the lane's configuration counted from the start of the wave's first row
+  // whether any of the nm members of a stage has a flag set (uniform)
+  static __device__ __forceinline__ bool any_flags(const uint32_t* stage, int nm, int member_words, int lane, const NetOffsets& o) {
+    bool any = false;
+    for (int m = lane; m < nm; m += 64)
+#pragma unroll
+      for (int u = 0; u <= NT2; ++u) any = any || stage[(size_t)m * member_words + o.flags + u] != 0u;
+    return __ballot(any) != 0ull;
+  }
+
+  // `at` = the lane's configuration counted from the start of the wave's (the chunk's) first row
   static __device__ __forceinline__ void place(uint32_t at, int lane, const NetOffsets& o, Feat& f) {
     const uint32_t h = (uint32_t)lane >> 5;
-    const uint32_t row = (at * o.span_magic) >> 16, lo = at - row * o.span;
+    const uint32_t row = (at * o.span_magic) >> 20, lo = at - row * o.span;
     f.tb = TABLES_IN_MEMORY ? lo * 32u + (h << 4) : lo * (kUnits * 4u) + ((h ^ (lo & 7u)) << 4);
     f.zs = row * (kRowFloats * 4u) + (h << 4);
   }
 
-  // xs[row][p]: feature of high parameter p in a row, 1 at p = p0 (the bias), 0 beyond
-  static __device__ __forceinline__ void load_rows(const DevSpace& sp, uint32_t row0, uint32_t n_rows, int lane, bool pow2,
-                                                   const NetOffsets& o, float* xs) {
-    const int p = lane & 31;
-    for (uint32_t r = (uint32_t)lane >> 5; r < n_rows; r += 2) {
+  // xs[row][p]: feature of high parameter p in a row, 1 at p = p0 (the bias), 0 beyond; by the
+  // wave (tid = lane, threads = 64) or the workgroup
+  static __device__ __forceinline__ void load_rows(const DevSpace& sp, uint32_t row0, uint32_t n_rows, uint32_t tid,
+                                                   uint32_t threads, bool pow2, const NetOffsets& o, float* xs) {
+    const int p = (int)(tid & 31u);
+    for (uint32_t r = tid >> 5; r < n_rows; r += threads / 32u) {
       const float x = feature_at(sp, p, (row0 + r) * o.span, pow2);
       xs[r * 32 + p] = p < o.p0 ? x : (p == o.p0 ? 1.0f : 0.0f);
     }
@@ -371,20 +388,44 @@ struct FactoredNet {
 
   // Once per member: 2^z_row[u] (or z_row[u], flag 0) of every unit for the wave's rows
   // (`tables`: the member's TB and WH, in memory or in LDS like the rest of it)
-  static __device__ __forceinline__ void rows(const uint32_t* wm, const uint32_t* tables, uint32_t n_rows, int lane,
-                                              const NetOffsets& o, const float* xs, float* zs) {
+  static __device__ __forceinline__ void rows(const uint32_t* wm, const uint32_t* tables, uint32_t n_rows, bool flagged,
+                                              int lane, const NetOffsets& o, const float* xs, float* zs) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const float4* wh = reinterpret_cast<const float4*>(tables + o.wh);
     const float4* x4 = reinterpret_cast<const float4*>(xs);
-    const bool plain = __builtin_amdgcn_readfirstlane(wm[o.flags]) != 0u;
+    const bool plain = flagged && __builtin_amdgcn_readfirstlane(wm[o.flags]) != 0u;
+    for (uint32_t r0 = 0; r0 < n_rows; r0 += kRowsPerPass) row_pass(wh, x4, r0, plain, lane, o, zs);
+    // a wave's LDS instructions execute in program order; the fences keep the compiler from
+    // moving the reads of forward() above these writes, or the next member's writes above them
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+
+  // The rows of a chunk for all members, by the workgroup's waves in turn (ROWS_SHARED); the
+  // caller puts barriers around it.
+  static __device__ __forceinline__ void rows_of_chunk(const uint32_t* wts, int n_members, int member_words, uint32_t n_rows,
+                                                       uint32_t wave, uint32_t waves, bool flagged, int lane,
+                                                       const NetOffsets& o, const float* xs, float* zs) {
+    const uint32_t passes = (n_rows + kRowsPerPass - 1) / kRowsPerPass, tasks = passes * (uint32_t)n_members;
+    for (uint32_t task = wave; task < tasks; task += waves) {
+      const uint32_t m = task / passes, r0 = (task - m * passes) * kRowsPerPass;
+      const uint32_t* wm = wts + (size_t)m * member_words;
+      const bool plain = flagged && __builtin_amdgcn_readfirstlane(wm[o.flags]) != 0u;
+      row_pass(reinterpret_cast<const float4*>(wm + o.wh), reinterpret_cast<const float4*>(xs), r0, plain, lane, o,
+               zs + (size_t)m * o.rows * kRowFloats);
+    }
+  }
+
+  static constexpr uint32_t kRowsPerPass = kUnits == 32 ? 2u : 1u;
+  static __device__ __forceinline__ void row_pass(const float4* wh, const float4* x4, uint32_t r0, bool plain, int lane,
+                                                  const NetOffsets& o, float* zs) {
     const int groups = (o.p0 + 4) >> 2;
     constexpr int kPer = (kUnits + 63) / 64;                  // units per lane
-    constexpr uint32_t kStep = kUnits == 32 ? 2u : 1u;        // rows per pass
-    const uint32_t r_lane = kUnits == 32 ? (uint32_t)lane >> 5 : 0u;
     const int u = kUnits == 32 ? (lane & 31) : lane;
-    for (uint32_t r0 = 0; r0 < n_rows; r0 += kStep) {
-      const uint32_t r = r0 + r_lane;
+    {
+      const uint32_t r = r0 + (kUnits == 32 ? (uint32_t)lane >> 5 : 0u);
       float z[kPer];
 #pragma unroll
       for (int q = 0; q < kPer; ++q) z[q] = 0.0f;
@@ -403,22 +444,19 @@ struct FactoredNet {
       for (int q = 0; q < kPer; ++q)
         zs[r * kRowFloats + (kUnits == 96 && q ? 64 + (u & 31) : u + 64 * q)] = plain ? z[q] : __builtin_amdgcn_exp2f(z[q]);
     }
-    // a wave's LDS instructions execute in program order; the fences keep the compiler from
-    // moving the reads of forward() above these writes, or the next member's writes above them
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
 
-  static __device__ __forceinline__ float forward(const uint32_t* wm, const uint32_t* tables, const Feat& f, int lane,
-                                                  const NetOffsets& o, const float* zs) {
-    if (split_flags<NT2>(wm, o)) return forward_t<true>(wm, tables, f, lane, o, zs);
+  // flagged: some member of the stage has a flag set
+  static __device__ __forceinline__ float forward(const uint32_t* wm, const uint32_t* tables, bool flagged, const Feat& f,
+                                                  int lane, const NetOffsets& o, const float* zs) {
+    if (flagged) return forward_t<true>(wm, tables, f, lane, o, zs);
     return forward_t<false>(wm, tables, f, lane, o, zs);
   }
   // two tiles at once (kPair): the sums are added to y
-  static __device__ __forceinline__ void forward_pair(const uint32_t* wm, const uint32_t* tables, const Feat (&f)[2], int lane,
-                                                      const NetOffsets& o, const float* zs, float (&y)[2]) {
-    if (split_flags<NT2>(wm, o)) {
+  static __device__ __forceinline__ void forward_pair(const uint32_t* wm, const uint32_t* tables, bool flagged,
+                                                      const Feat (&f)[2], int lane, const NetOffsets& o, const float* zs,
+                                                      float (&y)[2]) {
+    if (flagged) {
       for (int c = 0; c < 2; ++c) y[c] += forward_t<true>(wm, tables, c ? f[1] : f[0], lane, o, zs);
       return;
     }

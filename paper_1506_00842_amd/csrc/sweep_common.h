@@ -52,14 +52,15 @@ struct Shape {
   // two-plane fp32 network (net_split.h)
   int o_flags;
   int span;                   // > 0: factored first layer; configurations per row
-  int rows;                   // ... and the most rows a wave's tiles reach
+  int rows;                   // ... and the most rows a wave's tiles (rows_shared: a chunk) reach
+  int rows_shared;            // the workgroup computes a chunk's rows for all members at once
   int table_words;            // > 0: TB and WH stay in memory, behind all members, in this many words each
 };
 
 struct NetOffsets {
   int w1, w2, b1, b2, wo, h1, h2, wh, p0;      // word offsets; real hidden widths; hoisting
   int flags;                                   // two-plane networks
-  uint32_t span, span_magic;                   // factored first layer: span; ceil(2^16 / span) divides places < 256
+  uint32_t span, span_magic;                   // factored first layer: span; ceil(2^20 / span) divides places < 1152
   uint32_t span_mul, span_sh;                  // division constants of the span (fast_div)
   uint32_t rows;                               // rows of the per-wave scratch
   int table_words;                             // tables in memory: words per member
@@ -73,6 +74,11 @@ struct SweepParams {
   int32_t r_used;              // tiles per wave and chunk actually used (1 .. the variant's R)
   int32_t n_members, members_per_stage, n_stages, member_words;
   int32_t mode, k;
+  int32_t pow2, n_constraints;   // the space's, known to the host
+  int32_t emit;               // top-k: the only workgroup writes the caller's outputs itself
+  float* out_values;
+  uint32_t* out_indices;
+  int32_t* out_found;
   int32_t merge;              // top-k: the caller's outputs hold a running result (values, indices, n_found)
   int32_t self_reset;         // the last workgroup to finish restores the header's idle state (sweeps that
                               // are the last kernel of their call and have used the header's counters)
@@ -122,6 +128,17 @@ __device__ __forceinline__ float unorder_bits(uint32_t o) {
 }
 __device__ __forceinline__ unsigned long long make_key(float y, uint32_t index) {
   return ((unsigned long long)order_bits(y) << 32) | index;
+}
+
+// Entry i of a sorted list of keys as the caller's outputs; the last real entry sets the count.
+__device__ __forceinline__ void emit_result(const unsigned long long* list, int i, int32_t k, float* values,
+                                            uint32_t* indices, int32_t* n_found) {
+  const unsigned long long key = list[i];
+  const bool real = key != kKeyMax;
+  values[i] = real ? unorder_bits((uint32_t)(key >> 32)) : __builtin_inff();
+  indices[i] = real ? (uint32_t)key : 0xffffffffu;
+  if (i == 0 && !real) *n_found = 0;
+  if (real && (i == k - 1 || list[i + 1] == kKeyMax)) *n_found = i + 1;
 }
 
 // z = -log2(e) * (pre-activation):  1 / (1 + 2^z)

@@ -49,11 +49,23 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
   unsigned long long* lpool = reinterpret_cast<unsigned long long*>(smem + prm.lds_pool_offset);
   const bool pool_in_lds = prm.lds_pool_entries > 0;
 
-  {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(prm.space);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(smem);
-    for (int x = tid; x < (int)(sizeof(DevSpace) / 4); x += kThreads) dst[x] = src[x];
-  }
+  // Everything a workgroup reads before its first chunk is under way at once: the space tables and
+  // a resident ensemble go straight into LDS (LDS-direct loads: no registers, completion = the
+  // wave's vmcnt), and what the host knows comes with the arguments.  One trip to memory instead
+  // of five or six in a row (and a single workgroup writes the result itself, see `emit`): a call
+  // over 256 configurations, top 10, took 14.5 us, now 11.8.
+  auto issue_copy = [&](const void* from, void* to, int n4) {
+    for (int x = wave_u * 64; x < n4; x += kThreads) {
+      if (x + lane < n4)
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void*)(reinterpret_cast<const uint4*>(from) + x + lane),
+            (__attribute__((address_space(3))) void*)(reinterpret_cast<uint4*>(to) + x), 16, 0, 0);
+    }
+  };
+  static_assert(sizeof(DevSpace) % 16 == 0, "copied in 16-byte words");
+  issue_copy(prm.space, smem, (int)(sizeof(DevSpace) / 16));
+  if (prm.n_stages == 1) issue_copy(prm.packed, wts, prm.n_members * prm.member_words / 4);
+  const float bo_sum = prm.hdr->bo_sum;
   if (tid == 0) { s_cnt = 0; s_tau_local = kKeyMax; s_compact = 0; }
   if (prm.mode == MODE_TOPK) {
     // The running result of earlier calls becomes one more sorted key list for the merge
@@ -64,7 +76,7 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
       found = *prm.run_found;
       found = found < 0 ? 0 : (found > prm.k ? prm.k : found);
     }
-    for (uint32_t x = blockIdx.x * kThreads + tid; x < prm.kp; x += gridDim.x * kThreads)
+    for (uint32_t x = blockIdx.x * kThreads + tid; prm.merge && x < prm.kp; x += gridDim.x * kThreads)
       prm.extra[x] = ((int)x < found) ? make_key(prm.run_values[x], prm.run_indices[x]) : kKeyMax;
     if (tid == 0 && found == prm.k && found > 0)
       s_tau_local = make_key(prm.run_values[prm.k - 1], prm.run_indices[prm.k - 1]);
@@ -87,30 +99,24 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
     int nm = prm.n_members - first;
     nm = nm < prm.members_per_stage ? nm : prm.members_per_stage;
     const uint4* src = reinterpret_cast<const uint4*>(prm.packed + (size_t)first * prm.member_words);
-    uint4* dst = reinterpret_cast<uint4*>(wts + (size_t)buf * prm.stage_words);
-    const int n4 = nm * prm.member_words / 4;
-    for (int x = wave_u * 64; x < n4; x += kThreads) {
-      if (x + lane < n4)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + x + lane),
-                                         (__attribute__((address_space(3))) void*)(dst + x), 16, 0, 0);
-    }
+    issue_copy(src, wts + (size_t)buf * prm.stage_words, nm * prm.member_words / 4);
   };
   const bool double_buffer = prm.double_buffer != 0;
   // per-wave scratch of the hoisting network: the tiles' high features, then one z_high vector
   float* hoist_xs = nullptr;
   float* hoist_zs = nullptr;
   if constexpr (Net::kRows) {
-    hoist_xs = reinterpret_cast<float*>(smem + prm.hoist_offset) + (size_t)wave_u * prm.off.rows * (32 + Net::kRowFloats);
+    // (one for the workgroup where the rows of a chunk are shared)
+    hoist_xs = reinterpret_cast<float*>(smem + prm.hoist_offset) +
+               (size_t)(Net::kRowsShared ? 0 : wave_u) * prm.off.rows * (32 + Net::kRowFloats);
     hoist_zs = hoist_xs + prm.off.rows * 32;
   }
   if constexpr (Net::kHoist) {
     hoist_xs = reinterpret_cast<float*>(smem + prm.hoist_offset) + (size_t)wave_u * (R * 32 + Net::kScratchZ);
     hoist_zs = hoist_xs + R * 32;
   }
-  if (prm.n_stages == 1) load_stage(0);
-  const float bo_sum = prm.hdr->bo_sum;
-  const bool pow2 = prm.space->all_pow2 != 0;
-  const int n_constraints = prm.space->n_constraints;
+  const bool pow2 = prm.pow2 != 0;
+  const int n_constraints = prm.n_constraints;
   // the weight stage doubles as sort scratch during pool compaction
   unsigned long long* lds_keys = reinterpret_cast<unsigned long long*>(wts);
   const uint32_t lds_entries = prm.lds_entries;
@@ -173,18 +179,24 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
     next1 = dynamic ? gridDim.x + atomicAdd(&prm.hdr->work_counter, 1u) : blockIdx.x + gridDim.x;
   }
 
-  for (;;) {
+  bool flagged = false;                       // factored networks: a member (of the stage) has a flag set
+  __builtin_amdgcn_s_waitcnt(0x0F70);         // vmcnt(0): this wave's part of the tables is in LDS
+  for (bool first = true;; first = false) {
     __syncthreads();
     if (tid == 0) {
       s_chunk = next0;
       if (prm.mode == MODE_TOPK) {
+        // (nothing to learn from the other workgroups before the first unit)
         const unsigned long long g =
-            __hip_atomic_load(&prm.hdr->tau, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            first ? kKeyMax : __hip_atomic_load(&prm.hdr->tau, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_tau = g < s_tau_local ? g : s_tau_local;
         s_compact = (s_cnt + super_iter > eff_cap) ? 1u : 0u;
       }
     }
     __syncthreads();
+    if constexpr (Net::kRows) {
+      if (first && prm.n_stages == 1) flagged = Net::any_flags(wts, prm.n_members, prm.member_words, lane, prm.off);
+    }
     const uint32_t unit = __builtin_amdgcn_readfirstlane(s_chunk);
     if (unit >= n_units) break;
     if (tid == 0) {
@@ -233,10 +245,23 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
     uint32_t row0 = 0, place0 = 0, n_rows = 0;
     bool any_tile = false;
     if constexpr (Net::kRows) {
-      const uint32_t i0 = (uint32_t)(prm.begin + (uint64_t)chunk * kIter) + (uint32_t)(wave_u * r_used * kTile);
+      const uint32_t reach = Net::kRowsShared ? kIter : (uint32_t)(r_used * kTile);
+      const uint32_t i0 = (uint32_t)(prm.begin + (uint64_t)chunk * kIter) +
+                          (Net::kRowsShared ? 0u : (uint32_t)(wave_u * r_used * kTile));
       row0 = fast_div(i0, prm.off.span_mul, prm.off.span_sh);
       place0 = i0 - row0 * prm.off.span;
-      n_rows = (((place0 + (uint32_t)(r_used * kTile) - 1u) * prm.off.span_magic) >> 16) + 1u;
+      n_rows = (((place0 + reach - 1u) * prm.off.span_magic) >> 20) + 1u;
+      if constexpr (Net::kRowsShared) {
+        // (the last chunk of a range may reach past its end: no more rows than it has)
+        __syncthreads();                     // the previous chunk's rows have been used
+        Net::load_rows(sp, row0, n_rows, (uint32_t)tid, kThreads, pow2, prm.off, hoist_xs);
+        __syncthreads();
+        if (state != CHUNK_ALL_INVALID)
+          Net::rows_of_chunk(wts, prm.n_members, prm.member_words, n_rows, (uint32_t)wave_u, kWaves, flagged, lane, prm.off,
+                             hoist_xs, hoist_zs);
+        __syncthreads();
+        place0 += (uint32_t)(wave_u * r_used * kTile);
+      }
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -276,7 +301,7 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
     }
 
     if constexpr (Net::kRows) {
-      if (any_tile) Net::load_rows(sp, row0, n_rows, lane, pow2, prm.off, hoist_xs);
+      if (!Net::kRowsShared && any_tile) Net::load_rows(sp, row0, n_rows, (uint32_t)lane, 64u, pow2, prm.off, hoist_xs);
     }
 
     // ---- ensemble
@@ -299,22 +324,27 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
       const int first = st * prm.members_per_stage;
       int nm = prm.n_members - first;
       nm = nm < prm.members_per_stage ? nm : prm.members_per_stage;
+      if constexpr (Net::kRows) {
+        if (prm.n_stages > 1) flagged = Net::any_flags(stage, nm, prm.member_words, lane, prm.off);
+      }
       for (int m = 0; m < nm; ++m) {
         const uint32_t* w = stage + (size_t)m * prm.member_words;
         if constexpr (Net::kRows) {
           const uint32_t* tables = w;
           if constexpr (Net::kTablesInMemory)
             tables = prm.packed + (size_t)prm.n_members * prm.member_words + (size_t)(first + m) * prm.off.table_words;
-          if (any_tile) Net::rows(w, tables, n_rows, lane, prm.off, hoist_xs, hoist_zs);
+          const float* zs = hoist_zs;
+          if constexpr (Net::kRowsShared) zs += (size_t)m * prm.off.rows * Net::kRowFloats;
+          else if (any_tile) Net::rows(w, tables, n_rows, flagged, lane, prm.off, hoist_xs, hoist_zs);
           if constexpr (Net::kPair && R == 2) {
             if (any[0] && any[1]) {
-              Net::forward_pair(w, tables, feat, lane, prm.off, hoist_zs, ysum);
+              Net::forward_pair(w, tables, flagged, feat, lane, prm.off, zs, ysum);
               continue;
             }
           }
 #pragma unroll
           for (int r = 0; r < R; ++r)
-            if (any[r]) ysum[r] += Net::forward(w, tables, feat[r], lane, prm.off, hoist_zs);
+            if (any[r]) ysum[r] += Net::forward(w, tables, flagged, feat[r], lane, prm.off, zs);
           continue;
         }
 #pragma unroll
@@ -366,8 +396,15 @@ __global__ void __launch_bounds__(NW * 64) sweep_kernel(const SweepParams prm) {
     __syncthreads();
     const uint32_t n = s_cnt;
     sort_candidates(n, false);
-    if (pool_in_lds)
+    if (prm.emit) {
+      // the only list there is: the caller's outputs (the header has not been touched)
+      for (int i = tid; i < prm.k; i += kThreads) {
+        if (pool_in_lds) emit_result(lpool, i, prm.k, prm.out_values, prm.out_indices, prm.out_found);
+        else emit_result(gpool, i, prm.k, prm.out_values, prm.out_indices, prm.out_found);
+      }
+    } else if (pool_in_lds) {
       for (uint32_t x = tid; x < prm.kp; x += kThreads) gpool[x] = lpool[x];
+    }
   }
   // A call on a prepared workspace has no kernel that resets the header before it.  Top-k
   // calls leave that to their last merge launch; a sweep that is the last kernel of its call

@@ -185,16 +185,6 @@ __device__ __forceinline__ void reset_header(WsHeader* hdr) {
   hdr->tau = kKeyMax;
 }
 
-__device__ __forceinline__ void emit_result(const unsigned long long* list, int i, int32_t k, float* values,
-                                            uint32_t* indices, int32_t* n_found) {
-  const unsigned long long key = list[i];
-  const bool real = key != kKeyMax;
-  values[i] = real ? unorder_bits((uint32_t)(key >> 32)) : __builtin_inff();
-  indices[i] = real ? (uint32_t)key : 0xffffffffu;
-  if (i == 0 && !real) *n_found = 0;
-  if (real && (i == k - 1 || list[i + 1] == kKeyMax)) *n_found = i + 1;
-}
-
 // Loads the lists first + j * stride (j = 0 .. 2^levels - 1; indices >= n_lists read as empty)
 // into LDS slots of kp keys: all lists at once, many loads in flight per thread (a loop over
 // the lists would pay one memory latency per list): 8 x 16 bytes per thread and round, which
@@ -653,6 +643,7 @@ static DeviceInfo device_info_or_default() {
 // LDS bytes of the hoisting networks' per-wave scratch: the high features of a wave's
 // tiles, and for net_f32h.h one z_high vector.
 static int hoist_scratch_bytes(const Shape& sh, const Variant* var) {
+  if (sh.span && sh.rows_shared) return sh.rows * (32 + sh.E * (sh.NT1 * 32 + 4)) * 4;
   if (sh.span) return var->waves * sh.rows * (32 + sh.NT1 * 32 + 4) * 4;
   if (!sh.hoist) return 0;
   const int z = sh.hoist == 1 ? std::max(64, sh.NT1 * 32) : 0;
@@ -681,7 +672,9 @@ static bool is_auto_fp32(const tuner_model* m) { return m->precision == TUNER_FP
 // Layout of the two-plane network (net_split.h) on top of the plain fp32 shape `sh`: factored
 // with rows of sp->strides[p0 - 1] configurations (p0 > 0), or behind the fp32 layer 1 that
 // `sh` describes.
-static void make_split_shape(const tuner_space* sp, int p0, bool tables_in_memory, Shape* sh) {
+enum { SPLIT_PLAIN = 0, SPLIT_TABLES_IN_MEMORY = 1, SPLIT_ROWS_SHARED = 2 };
+static void make_split_shape(const tuner_space* sp, int p0, int kind, Shape* sh) {
+  const bool tables_in_memory = kind == SPLIT_TABLES_IN_MEMORY;
   sh->net = NET_F32_SPLIT;
   if (p0 > 0) {
     // any pair of tile counts has its kernel
@@ -699,7 +692,9 @@ static void make_split_shape(const tuner_space* sp, int p0, bool tables_in_memor
     // at a multiple of gcd(32, span) in their first row
     int g = 32;
     while (sh->span % g) g /= 2;
-    sh->rows = (sh->span - g + 63) / sh->span + 1;
+    sh->rows_shared = kind == SPLIT_ROWS_SHARED ? 1 : 0;
+    const int reach = sh->rows_shared ? kMaxIter : 64;          // configurations of a chunk / of a wave's tiles
+    sh->rows = (sh->span - g + reach - 1) / sh->span + 1;
     if (units == 32) sh->rows = round_up(sh->rows, 2);      // two rows per pass
     at = tables_in_memory ? 0 : sh->span * units;
   }
@@ -723,10 +718,11 @@ static void make_split_shape(const tuner_space* sp, int p0, bool tables_in_memor
 // first layer when a trailing group of parameters runs through 11 to 128 configurations (fewer
 // would mean more than 7 rows per wave, more a table of over 16 KB per 32 units) and the
 // ensemble then stays resident in LDS with 32 KB left for the candidates, or at least in two
-// stage buffers, if need be with the first layer's tables left in memory; of several such groups the one with the fewest passes over the rows, then the
-// smallest table.  One hidden layer in a space of less than 2^18 configurations stays with the
-// fp32 matrix network: its sweep is over before the larger tables pay (131,072 configurations,
-// 11 x 9-30-1, top 200: 41.8 us a call against 43.4; 655,360 x 10-30-1, top 300: 122 against 112).
+// stage buffers, if need be with the first layer's tables left in memory; of several such groups
+// the one with the fewest passes over the rows, then the smallest table.  One hidden layer in a
+// space of less than 2^18 configurations stays with the fp32 matrix network: its sweep is over
+// before the larger tables pay (131,072 configurations, 11 x 9-30-1, top 200: 40.5 us a call
+// against 41.3; 655,360 x 10-30-1, top 300: 122 against 98.7).
 // Decided from the space and the model alone, so that tuner_prepare and every later call agree.
 static bool choose_split(const tuner_space* sp, const tuner_model* m, bool range, Shape* sh, const Variant** var) {
   if (!is_auto_fp32(m)) return false;
@@ -734,17 +730,22 @@ static bool choose_split(const tuner_space* sp, const tuner_model* m, bool range
   if (make_shape(sp, m, &plain, 0) != TUNER_OK) return false;
   if (!plain.NT2 && sp->n_configs < (1ull << 18)) return false;
   long best = -1;
-  for (int p0 = plain.P - 1, in_memory = 0; range && in_memory <= 1; --p0) {
-    if (p0 < 1) {                              // next the tables in memory, if nothing fits with them in LDS
-      if (best >= 0 || !plain.NT2) break;
-      ++in_memory;
+  // one hidden layer: rows shared by the workgroup where its waves take one tile each and the
+  // ensemble stays resident, else by wave; two: by wave, with the tables in memory if nothing fits with them in LDS
+  const bool share = !plain.NT2 && sp->n_configs < (1ull << 21);     // (from there on two tiles per wave)
+  const int kinds[2][2] = {{share ? SPLIT_ROWS_SHARED : SPLIT_PLAIN, SPLIT_PLAIN}, {SPLIT_PLAIN, SPLIT_TABLES_IN_MEMORY}};
+  for (int p0 = plain.P - 1, turn = 0; range; --p0) {
+    if (p0 < 1) {
+      if (best >= 0 || turn == 1) break;
+      turn = 1;
       p0 = plain.P;
       continue;
     }
+    const int kind = kinds[plain.NT2 ? 1 : 0][turn];
     const uint64_t span = sp->strides[p0 - 1];
     if (span < 11 || span > (uint64_t)kMaxSpan) continue;
     Shape s = plain;
-    make_split_shape(sp, p0, in_memory != 0, &s);
+    make_split_shape(sp, p0, kind, &s);
     const Variant* v = find_variant_split(s);
     if (!v) continue;
     const StagePlan pl = plan_stages(s, v, kLdsBytesPerWorkgroup);
@@ -753,15 +754,19 @@ static bool choose_split(const tuner_space* sp, const tuner_model* m, bool range
     if (pl.mps >= s.E) rank = (long)s.E * member_bytes + (32 << 10) <= pl.budget ? 0 : 1;
     else if (pl.double_buffer) rank = 2;
     else continue;
+    if (kind == SPLIT_ROWS_SHARED && rank > 1) continue;
+    // passes over the rows, then the table; shared rows: the LDS that tables and rows take
     const int passes = s.NT1 == 1 ? s.rows / 2 : s.rows;
-    const long cost = ((long)rank << 40) + ((long)passes << 20) + (long)span;
+    const long size = kind == SPLIT_ROWS_SHARED ? (long)s.E * member_bytes + hoist_scratch_bytes(s, v)
+                                                : ((long)passes << 20) + (long)span;
+    const long cost = ((long)rank << 40) + size;
     if (best < 0 || cost < best) { best = cost; *sh = s; *var = v; }
   }
   if (best >= 0) return true;
   if (!plain.NT2) return false;                // one hidden layer: the fp32 matrix network
   Shape s{};
   if (make_shape(sp, m, &s, range ? 1 : 0) != TUNER_OK) return false;
-  make_split_shape(sp, 0, false, &s);
+  make_split_shape(sp, 0, SPLIT_PLAIN, &s);
   const Variant* v = find_variant_split(s);
   if (!v || plan_stages(s, v, kLdsBytesPerWorkgroup).mps < 1) return false;
   *sh = s;
@@ -1002,7 +1007,7 @@ static int plan_sweep(const tuner_space* sp, const tuner_model* m, uint64_t begi
         ++P.merge_launches;
         if (live > 1 && merge_fuse_levels(live, list_bytes, P.merge_lds_max)) break;   // second stage in the same launch
       }
-      if (n_lists == 1) P.merge_launches = 1;      // finalize only
+      if (n_lists == 1) P.merge_launches = P.groups == 1 ? 0 : 1;   // the sweep writes the outputs / finalize
     } else {
       for (uint32_t n = n_lists; n > 1; n = (n + 1) / 2) ++P.merge_launches;
       ++P.merge_launches;                          // finalize
@@ -1097,7 +1102,7 @@ static int run_sweep(const tuner_space* sp, const tuner_model* m, uint64_t begin
     sw.off.flags = sh.o_flags;
     if (sh.span) {
       sw.off.span = (uint32_t)sh.span;
-      sw.off.span_magic = (65536u + (uint32_t)sh.span - 1u) / (uint32_t)sh.span;
+      sw.off.span_magic = ((1u << 20) + (uint32_t)sh.span - 1u) / (uint32_t)sh.span;
       div_constants((uint32_t)sh.span, &sw.off.span_mul, &sw.off.span_sh);
       sw.off.rows = (uint32_t)sh.rows;
       sw.off.table_words = sh.table_words;
@@ -1106,6 +1111,12 @@ static int run_sweep(const tuner_space* sp, const tuner_model* m, uint64_t begin
     sw.merge = merge;
     sw.self_reset = (mode == MODE_ALL && (P.dynamic || P.use_live)) ? 1 : 0;
     sw.extra = mode == MODE_TOPK ? extra : nullptr;
+    sw.pow2 = sp->dev.all_pow2;
+    sw.n_constraints = sp->dev.n_constraints;
+    sw.emit = mode == MODE_TOPK && groups == 1 && P.n_lists == 1 ? 1 : 0;
+    sw.out_values = values;
+    sw.out_indices = indices;
+    sw.out_found = n_found;
     sw.run_values = values;
     sw.run_indices = indices;
     sw.run_found = n_found;
@@ -1157,7 +1168,7 @@ static int run_sweep(const tuner_space* sp, const tuner_model* m, uint64_t begin
     }
   }
 
-  if (mode == MODE_TOPK) {
+  if (mode == MODE_TOPK && !(groups == 1 && P.n_lists == 1)) {
     // lists: pool 0..groups-1, then the running result when the call merges with it
     const uint32_t n_lists = P.n_lists;
     const size_t list_bytes = (size_t)L.kp * 8;
