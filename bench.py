@@ -200,8 +200,8 @@ def main():
     ap.add_argument("--workload", default="cfg3",
                     help="cfg1..cfg5, cfg3-2^26, paper-convolution, paper-raycasting, paper-stereo")
     ap.add_argument("--mode", default="topk", choices=["topk", "all"])
-    ap.add_argument("--net", default="f32-mfma", choices=["f32-mfma", "split16", "bf16", "valu"],
-                    help="f32-mfma: fp32 matrix instructions; split16: two-plane f16 split, fp32 "
+    ap.add_argument("--net", default="auto", choices=["auto", "f32-mfma", "split16", "bf16", "valu"],
+                    help="auto: fp32, the library's choice; f32-mfma: fp32 matrix instructions; split16: two-plane f16 split, fp32 "
                          "accumulate (fp32 tolerance); bf16: bf16 operands (1e-2 tolerance)")
     ap.add_argument("--graph", action="store_true",
                     help="capture one step in a HIP graph and time its replays (the sweep kernel's own "
@@ -333,7 +333,7 @@ def main():
         # the same workload with the other network evaluations (3 steps each, outside the
         # timed region above): context for the choice of the matrix-core path
         others = {}
-        for name in ("f32-mfma", "split16", "valu", "bf16"):
+        for name in ("auto", "f32-mfma", "split16", "valu", "bf16"):
             if name == args.net:
                 continue
             sw2 = Sweep(sp, m, w.k, **net_kwargs(T, name))
@@ -342,7 +342,7 @@ def main():
                             "tolerance": 1e-2 if name == "bf16" else 1e-5}
             del sw2
         out["other_nets"] = others
-    if not args.no_other_workloads and args.workload == "cfg3" and args.mode == "topk" and args.net == "f32-mfma":
+    if not args.no_other_workloads and args.workload == "cfg3" and args.mode == "topk" and args.net == "auto":
         out["other_workloads"] = other_workloads(T, torch, wl, Sweep, stream)
     if not args.no_cpu:
         out["cpu_baseline"] = cpu_baseline(w)
@@ -350,7 +350,8 @@ def main():
 
 
 def net_kwargs(T, net):
-    return {"f32-mfma": dict(precision=T.TUNER_FP32, algo=T.TUNER_ALGO_MFMA),
+    return {"auto": dict(precision=T.TUNER_FP32, algo=T.TUNER_ALGO_AUTO),
+            "f32-mfma": dict(precision=T.TUNER_FP32, algo=T.TUNER_ALGO_MFMA),
             "split16": dict(precision=T.TUNER_FP32, algo=T.TUNER_ALGO_SPLIT16),
             "valu": dict(precision=T.TUNER_FP32, algo=T.TUNER_ALGO_VALU),
             "bf16": dict(precision=T.TUNER_BF16_MFMA, algo=T.TUNER_ALGO_AUTO)}[net]
@@ -400,19 +401,29 @@ def roofline_of(T, sw, w, net, kernel_ms, launches_per_step):
     executed counts: configurations the sweep skips (invalid ones) count for nothing, and the
     layer-1 multiply-adds of the parameters that are constant over a tile of 32 configurations
     count once per tile, those read from the per-member table not at all.  The figure with
-    every evaluated configuration's full network is kept as `frac_algorithmic`."""
+    every evaluated configuration's full network is kept as `frac_algorithmic`.  The library's own
+    fp32 choice (`auto`) executes the second hidden layer as three f16 matrix products (counted
+    against the f16 matrix peak; the kernel itself is bound by the sigmoids on the vector ALU) and
+    layer 1 as one multiply-add per unit."""
     m = w.model
     if w.n_valid < 0 or kernel_ms <= 0:
         return None
     flop_per_cfg = 2 * m.macs_per_config
     n_hoisted = T.tuner_hoisted_parameters(sw.space, sw.model)
     executed = flop_per_cfg - 2.0 * m.n_members * m.widths[1] * n_hoisted * 31.0 / 32.0
-    n_tabulated = T.tuner_tabulated_parameters(sw.space, sw.model) if net == "f32-mfma" else 0
-    if n_tabulated:
+    n_tabulated = T.tuner_tabulated_parameters(sw.space, sw.model) if net in ("auto", "f32-mfma") else 0
+    if n_tabulated and net == "f32-mfma":
         # one matrix step (2 inputs) adds the tile's vector to the table
         executed -= 2.0 * m.n_members * m.widths[1] * (n_tabulated - 2)
     peak = PEAK_BF16_MATRIX_TFLOPS if net == "bf16" else PEAK_FP32_MATRIX_TFLOPS
     bound = "mfma"
+    if net == "auto":
+        h1, h2 = m.widths[1], m.widths[2] if len(m.widths) == 4 else 0
+        executed = m.n_members * (2.0 * h1 + (6.0 * h1 * h2 + 2.0 * h2 if h2 else 2.0 * h1))
+        if h2:
+            peak = PEAK_BF16_MATRIX_TFLOPS
+        else:
+            bound, peak = "alu", PEAK_FP32_VECTOR_FMA_TFLOPS
     if net == "split16":          # three f16 matrix products per fp32 product, against the f16 matrix peak
         executed *= 3.0
         peak = PEAK_BF16_MATRIX_TFLOPS
@@ -423,7 +434,8 @@ def roofline_of(T, sw, w, net, kernel_ms, launches_per_step):
     algorithmic = evaluated_per_launch * flop_per_cfg / (kernel_ms * 1e-3) / 1e12
     return {"bound": bound, "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
             "traffic": None,
-            "kernel": {"f32-mfma": "sweep_kernel (fp32 MFMA 32x32x2)", "bf16": "sweep_kernel (bf16 MFMA 32x32x16)",
+            "kernel": {"auto": "sweep_kernel (fp32: two-plane f16 MFMA 32x32x16 behind a factored layer 1)",
+                       "f32-mfma": "sweep_kernel (fp32 MFMA 32x32x2)", "bf16": "sweep_kernel (bf16 MFMA 32x32x16)",
                        "split16": "sweep_kernel (f16 MFMA 32x32x16, two planes)", "valu": "sweep_kernel (v_fma_f32)"}[net],
             "kernel_ms": kernel_ms, "launches_per_step": launches_per_step,
             "evaluated_configs_per_launch": evaluated_per_launch,
@@ -459,17 +471,17 @@ def other_workloads(T, torch, wl, Sweep, stream):
             e["hbm_write_GBs"] = 4.0 * N / (ms * 1e-3) / 1e9
         res[name] = e
 
-    leg("cfg3-predict_all", wl.large(), "f32-mfma", "all", 5, 1)
-    leg("cfg4-f32", wl.wide(), "f32-mfma", "topk", 3, 1)
+    leg("cfg3-predict_all", wl.large(), "auto", "all", 5, 1)
+    leg("cfg4-f32", wl.wide(), "auto", "topk", 3, 1)
     leg("cfg4-bf16", wl.wide(), "bf16", "topk", 5, 1)
-    leg("cfg5-streamed-16-chunks", wl.streamed(), "f32-mfma", "topk", 2, 1)
+    leg("cfg5-streamed-16-chunks", wl.streamed(), "auto", "topk", 2, 1)
     # short sweeps: latency per call (no roofline fraction: they are bound by fixed costs), with
     # the packing kernel in every call and with the workspace prepared once
     for prepared in (False, True):
         tag = "-prepared" if prepared else ""
-        leg("cfg1-tiny" + tag, wl.tiny(), "f32-mfma", "topk", 200, 20, prepared)
-        leg("cfg2-conv-shaped" + tag, wl.conv_shaped(), "f32-mfma", "topk", 200, 20, prepared)
-        leg("paper-convolution" + tag, wl.paper_convolution(), "f32-mfma", "topk", 200, 20, prepared)
+        leg("cfg1-tiny" + tag, wl.tiny(), "auto", "topk", 200, 20, prepared)
+        leg("cfg2-conv-shaped" + tag, wl.conv_shaped(), "auto", "topk", 200, 20, prepared)
+        leg("paper-convolution" + tag, wl.paper_convolution(), "auto", "topk", 200, 20, prepared)
     return res
 
 
