@@ -280,7 +280,8 @@ int tuner_predict_all_prepared(const tuner_space* space, const tuner_model* mode
  * on the host side of the GPU or on the device.
  *   - A space, model and k whose tuner_workspace_bytes() exceeds
  *     TUNER_STATIC_SCRATCH_BYTES is refused with TUNER_ETOOLARGE (the message
- *     gives both sizes); the five benchmark configurations fit.
+ *     gives both sizes); the five benchmark configurations fit.  A model with
+ *     TUNER_ALGO_AUTO that would not fit runs as TUNER_ALGO_MFMA where that fits.
  *   - Every call on a GPU uses that GPU's one array: calls that may run at the
  *     same time on one GPU (different streams, different threads) race.  Calls
  *     ordered on one stream are safe; nothing needs to be cleared between them.

@@ -1439,6 +1439,15 @@ int tuner_predict_topk_static(const tuner_space* space, const tuner_model* model
   size_t need = 0;
   int rc = workspace_need(space, model, k, &need);
   if (rc) return rc;
+  // The tables of layer-1 factors make a member larger, so that ensembles of hundreds of members
+  // could leave the array's size: those run on the fp32 matrix network, whose members are smaller.
+  tuner_model smaller = *model;
+  if (need > (size_t)TUNER_STATIC_SCRATCH_BYTES && tuner::is_auto_fp32(model)) {
+    smaller.algo = TUNER_ALGO_MFMA;
+    model = &smaller;
+    rc = workspace_need(space, model, k, &need);
+    if (rc) return rc;
+  }
   if (need > (size_t)TUNER_STATIC_SCRATCH_BYTES)
     return set_error(TUNER_ETOOLARGE,
                      "this space, model and k need " + std::to_string(need) + " bytes of scratch, more than the " +

@@ -143,3 +143,23 @@ def test_list_evaluation():
     ry, rv = oracle.predict_indices(sp, m, idx, threads=THREADS)
     assert np.array_equal(mi.cpu().numpy(), rv)
     parity.check_predictions(pi.cpu().numpy(), ry, rv)
+
+
+@pytest.mark.parametrize("members,hidden", [(64, [128, 128]), (512, [64, 64]), (2000, [30])])
+def test_static_scratch_keeps_ensembles_whose_tables_outgrow_it(members, hidden):
+    """Their workspace exceeds the static array, the fp32 matrix network's does not: the call
+    runs on that one, bit for bit."""
+    import paper_1506_00842_amd as T
+    from paper_1506_00842_amd.api import Sweep
+    sp = space_with_tail((3,) * 16, (3,) * 4)
+    m = wl.make_model([sp.n_params, *hidden, 1], members, 3)
+    k, begin, count = 10, 1000003, 700
+    auto = Sweep(sp, m, k)
+    ref = Sweep(sp, m, k, algo=T.TUNER_ALGO_MFMA)
+    assert T.tuner_workspace_bytes(auto.space, auto.model, k) > T.TUNER_STATIC_SCRATCH_BYTES
+    assert T.tuner_workspace_bytes(ref.space, ref.model, k) <= T.TUNER_STATIC_SCRATCH_BYTES
+    T.tuner_predict_topk_static(auto.space, auto.model, begin, count, k, 0, auto.values, auto.indices, auto.n_found)
+    ref.topk(begin, count)
+    torch.cuda.synchronize()
+    assert int(ref.n_found.item()) == k and torch.equal(auto.n_found, ref.n_found)
+    assert torch.equal(auto.values, ref.values) and torch.equal(auto.indices, ref.indices)
