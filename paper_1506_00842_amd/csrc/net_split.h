@@ -560,23 +560,46 @@ struct PackScratch {
   uint32_t any;
 };
 constexpr int kMaxSpan = 128;
-constexpr int kTableSlice = 2048;             // words of TB one workgroup writes
-__host__ __device__ inline int split_table_slices(const Shape& sh) {
-  return sh.span ? (sh.span * sh.NT1 * 32 + kTableSlice - 1) / kTableSlice : 0;
+// Words of TB one workgroup writes: the more workgroups the shorter the chain, until the members
+// alone fill the chip (500 members of 64 units, 100 configurations: 745 us with 512, 730 with 2048).
+__host__ __device__ inline int split_table_slice(const Shape& sh) { return sh.E >= 128 ? 2048 : 512; }
+// Workgroups that pack a member's factored first layer: one per slice of TB, and one for the rest.
+__host__ __device__ inline int split_table_jobs(const Shape& sh) {
+  return sh.span ? (sh.span * sh.NT1 * 32 + split_table_slice(sh) - 1) / split_table_slice(sh) + 1 : 0;
 }
 
-// A workgroup of 256 threads writes one slice of TB of one member (factored layout), the first
-// one also WH, b2A, woA and flag 0.  Everything is read into LDS first, in one trip to memory.
+// put(x, src[x]) for x = 0 .. n - 1 by 256 threads, eight loads of a thread in flight.
+template <class Put>
+__device__ __forceinline__ void stage_words(const float* src, int n, Put put) {
+  for (int x0 = (int)threadIdx.x; x0 < n; x0 += 8 * 256) {
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = src[min(x0 + 256 * q, n - 1)];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (x0 + 256 * q < n) put(x0 + 256 * q, v[q]);
+  }
+}
+
+// A workgroup of 256 threads writes one slice of TB of one member (factored layout), the last
+// one WH, b2A, woA and flag 0 instead.  Everything is read into LDS first, in one trip to memory.
+// What bounds it is the chain of one thread (a double-precision sum and exp2 per word), so the
+// slices are short: with 512 words instead of 2048 the packing of 11 x (11-30-1) takes 5.5 us
+// instead of 8.1.
 // `tables`: where the member's TB and WH go (the member itself, or its place behind all members).
 __device__ inline void pack_factored(const Shape& sh, const float* raw, uint32_t* member, uint32_t* tables, const DevSpace& sp,
                                      int slice, PackScratch& s) {
   const int tid = threadIdx.x, units = sh.NT1 * 32, n_low = sh.P - sh.p0;
   const bool pow2 = sp.all_pow2 != 0;
   if (tid == 0) s.any = 0u;
-  for (int x = tid; x < sh.H1 * (sh.P + 1); x += 256) s.w[x] = raw[x];       // W1, then b1
-  for (int x = tid; x < sh.span * n_low; x += 256) {
+  stage_words(raw, sh.H1 * (sh.P + 1), [&](int x, float v) { s.w[x] = v; });       // W1, then b1
+  const bool rest = slice == split_table_jobs(sh) - 1;
+  const int begin = slice * split_table_slice(sh);
+  const int end = rest ? begin : min(begin + split_table_slice(sh), sh.span * units);
+  const int l0 = begin / units, n_x = rest ? 0 : ((end - 1) / units - l0 + 1) * n_low;   // the slice's places
+  for (int x = tid; x < n_x; x += 256) {
     const int l = x / n_low;
-    s.x[x] = feature_at(sp, sh.p0 + (x - l * n_low), (uint32_t)l, pow2);
+    s.x[x] = feature_at(sp, sh.p0 + (x - l * n_low), (uint32_t)(l0 + l), pow2);
   }
   const float* b1 = s.w + sh.H1 * sh.P;
   __syncthreads();
@@ -587,19 +610,18 @@ __device__ inline void pack_factored(const Shape& sh, const float* raw, uint32_t
   }
   __syncthreads();
   const bool plain = s.any != 0u;
-  const int end = min((slice + 1) * kTableSlice, sh.span * units);
-  for (int x = slice * kTableSlice + tid; x < end; x += 256) {
+  for (int x = begin + tid; x < end; x += 256) {
     const int l = x / units, u = x - l * units;
     double z = 0.0;
     if (u < sh.H1)
-      for (int p = 0; p < n_low; ++p) z = fma((double)s.w[u * sh.P + sh.p0 + p], (double)s.x[l * n_low + p], z);
+      for (int p = 0; p < n_low; ++p) z = fma((double)s.w[u * sh.P + sh.p0 + p], (double)s.x[(l - l0) * n_low + p], z);
     z *= kNegLog2eD;
     const int t = u >> 5, e = (u >> 2) & 7, j = u & 3;
     const int at = sh.table_words ? ((t * 4 + (e >> 1)) * sh.span + l) * 8 + (e & 1) * 4 + j
                                   : l * units + 32 * t + 4 * (e ^ (l & 7)) + j;
     tables[at] = __float_as_uint(plain ? (float)z : exp2_of(z));
   }
-  if (slice != 0) return;
+  if (!rest) return;
   if (tid == 0) member[sh.o_flags] = plain ? 1u : 0u;
   const int groups = (sh.p0 + 4) / 4;
   for (int x = tid; x < groups * units * 4; x += 256) {
@@ -619,7 +641,9 @@ __device__ inline void pack_factored(const Shape& sh, const float* raw, uint32_t
 }
 
 // A workgroup of 256 threads writes the 32 rows (output units) of tile u of layer 2, both f16
-// planes or fp32, and flag 1 + u.
+// planes or fp32, and flag 1 + u.  Bound by the trips to memory of its first loop and by LDS: with
+// eight loads in flight and an odd row pitch 16 members of 14-128-128-1 take 10.9 us instead of
+// 13.1, 4 of 14-64-64-1 6.7 instead of 8.3.
 __device__ inline void pack_split_w2(const Shape& sh, const float* raw, uint32_t* member, int u, PackScratch& s) {
   const int tid = threadIdx.x;
   const int r_w2 = sh.H1 * sh.P + sh.H1;
@@ -627,11 +651,12 @@ __device__ inline void pack_split_w2(const Shape& sh, const float* raw, uint32_t
   if (tid == 0) s.any = 0u;
   __syncthreads();
   bool fits = true;
-  for (int x = tid; x < n_rows * sh.H1; x += 256) {
-    const float w = raw[r_w2 + 32 * u * sh.H1 + x];
-    s.w[x] = w;
+  const int pitch = sh.H1 | 1;                                  // odd: the lanes of a wave read 32 rows at once
+  stage_words(raw + r_w2 + 32 * u * sh.H1, n_rows * sh.H1, [&](int x, float w) {
+    const int n = x / sh.H1;
+    s.w[n * pitch + (x - n * sh.H1)] = w;
     fits = fits && fabsf(w) * -kNegLog2e <= kSplitMaxWeight;    // false for NaN
-  }
+  });
   if (!fits) atomicOr(&s.any, 1u);
   __syncthreads();
   const bool fp32 = s.any != 0u;
@@ -645,7 +670,7 @@ __device__ inline void pack_split_w2(const Shape& sh, const float* raw, uint32_t
       for (int k = 0; k < 2; ++k) {
         const int j = 2 * jj + k, in = 16 * kbg + 8 * (j >> 2) + 4 * h + (j & 3);
         if (n < n_rows && in < sh.H1) {
-          const double v = (double)s.w[n * sh.H1 + in] * kNegLog2eD;
+          const double v = (double)s.w[n * pitch + in] * kNegLog2eD;
           const _Float16 a = (_Float16)(float)v;
           const _Float16 r = (_Float16)(float)(v - (double)(float)a);
           hi |= (uint32_t)__builtin_bit_cast(uint16_t, a) << (16 * k);
@@ -657,7 +682,7 @@ __device__ inline void pack_split_w2(const Shape& sh, const float* raw, uint32_t
       for (int k = 0; k < 2; ++k) {
         const int q = x + k * half, j = q & 3, lane = (q >> 2) & 63, g = (q >> 8) & 3, t = q >> 10;
         const int n = lane & 31, in = 32 * t + 8 * g + 4 * (lane >> 5) + j;
-        const float v = n < n_rows && in < sh.H1 ? s.w[n * sh.H1 + in] * kNegLog2e : 0.0f;
+        const float v = n < n_rows && in < sh.H1 ? s.w[n * pitch + in] * kNegLog2e : 0.0f;
         (k ? lo : hi) = __float_as_uint(v);
       }
     }

@@ -104,12 +104,12 @@ __global__ void __launch_bounds__(256) prep_kernel(const DevSpace sp, const Prep
 }
 
 // The same for the two-plane networks (net_split.h): the first workgroups write a slice of a
-// member's factored first layer each, the next a 32-row tile of a second layer each, the rest
+// member's factored first layer each (the last of a member its small arrays), the next a 32-row tile of a second layer each, the rest
 // the words that stand for themselves, the space tables and the header.
 __global__ void __launch_bounds__(256) prep_split_kernel(const DevSpace sp, const PrepParams pp) {
   __shared__ PackScratch scratch;
   const Shape& sh = pp.sh;
-  const uint32_t slices = (uint32_t)split_table_slices(sh);
+  const uint32_t slices = (uint32_t)split_table_jobs(sh);
   const uint32_t n_tables = (uint32_t)sh.E * slices, n_tiles = (uint32_t)(sh.E * sh.NT2);
   uint32_t b = blockIdx.x;
   if (b < n_tables) {
@@ -833,7 +833,7 @@ static int launch_prep(const tuner_space* sp, const tuner_model* m, const Shape&
   const uint32_t total_packed = (uint32_t)sh.E * sh.member_words;
   const unsigned prep_blocks = std::min<unsigned>(1024, (total_packed + 255) / 256);
   if (sh.net == NET_F32_SPLIT) {
-    const unsigned jobs = (unsigned)sh.E * (unsigned)(split_table_slices(sh) + sh.NT2);
+    const unsigned jobs = (unsigned)sh.E * (unsigned)(split_table_jobs(sh) + sh.NT2);
     hipLaunchKernelGGL(prep_split_kernel, dim3(jobs + (sh.span ? 4u : prep_blocks)), dim3(256), 0, stream, sp->dev, pp);
   } else {
     hipLaunchKernelGGL(prep_kernel, dim3(prep_blocks), dim3(256), 0, stream, sp->dev, pp);
