@@ -720,9 +720,10 @@ static void make_split_shape(const tuner_space* sp, int p0, int kind, Shape* sh)
 // ensemble then stays resident in LDS with 32 KB left for the candidates, or at least in two
 // stage buffers, if need be with the first layer's tables left in memory; of several such groups
 // the one with the fewest passes over the rows, then the smallest table.  One hidden layer in a
-// space of less than 2^18 configurations stays with the fp32 matrix network: its sweep is over
-// before the larger tables pay (131,072 configurations, 11 x 9-30-1, top 200: 40.5 us a call
-// against 41.3; 655,360 x 10-30-1, top 300: 122 against 98.7).
+// space of less than 2^18 configurations stays with the fp32 matrix network: there the shorter
+// sweep hardly makes up for the longer packing (131,072 configurations, 11 x 9-30-1, top 200: 40.5 us
+// a call against 39.9, and 2 us more for a call over a small part of the space; 655,360 x 10-30-1,
+// top 300: 122 against 98).
 // Decided from the space and the model alone, so that tuner_prepare and every later call agree.
 static bool choose_split(const tuner_space* sp, const tuner_model* m, bool range, Shape* sh, const Variant** var) {
   if (!is_auto_fp32(m)) return false;
