@@ -58,9 +58,12 @@ def test_mean_relative_error_alignment(n, offset_pred, offset_time):
 
 @pytest.mark.parametrize("y,t", [(0.5, 1e-40), (-85.0, 1e-37), (-100.0, 3e-39), (0.5, 3e38), (88.0, 1.0), (88.0, 2e38),
                                  (89.0, 1.0), (-200.0, 1.0), (79.0, 1e34), (-79.0, 1e-34), (0.0, 1.0)])
-def test_mean_relative_error_range(y, t):
+@pytest.mark.parametrize("n", [1, 16_383, 16_384])        # alone, or among failed runs in the short and the long form
+def test_mean_relative_error_range(n, y, t):
     y, t = np.float32(y), np.float32(t)
-    mean, used = tuner_for(wl.tiny().space).mean_relative_error(torch.tensor([float(y)]).cuda(), torch.tensor([float(t)]).cuda())
+    pred, times = torch.zeros(n), torch.full((n,), -1.0)
+    pred[n // 3], times[n // 3] = float(y), float(t)
+    mean, used = tuner_for(wl.tiny().space).mean_relative_error(pred.cuda(), times.cuda())
     with np.errstate(over="ignore"):
         want = float(np.float32(np.abs(np.float64(np.float32(np.exp(np.float64(y)))) - np.float64(t)) / np.float64(t)))
     assert int(used.item()) == 1
